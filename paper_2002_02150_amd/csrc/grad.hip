@@ -10,58 +10,133 @@
 
 namespace fcas {
 
-// Blocks (point, detector, part): each part sums a strided share of the
-// in-band bins into six complex FP64 partial sums; the chain kernel adds the
-// parts in a fixed order (deterministic).
-template <typename Real>
-__global__ void __launch_bounds__(256) k_adjoint_sums(const SegDesc* __restrict__ segs,
-                                                      const EvalDesc* __restrict__ evals,
-                                                      const int32_t* __restrict__ argmax, int n_det, int parts,
-                                                      double* __restrict__ sums) {
-  const int e = blockIdx.x, i = blockIdx.y, part = blockIdx.z;
+// Sums NV doubles per lane over the 64 lanes of a wavefront: while the count
+// is even, half of the values go to the other half of the lanes (NV/2
+// exchanges instead of NV), the rest is a butterfly.  `base` receives the
+// index of the lane's first total, the count of totals it holds is returned
+// (v[0 .. count)); lanes whose low bits agree hold the same totals.
+template <int NV, int OFF>
+__device__ __forceinline__ int wave_totals(double* v, int lane, int& base) {
+  if constexpr (OFF == 0) {
+    return NV;
+  } else if constexpr (NV % 2 == 0) {
+    constexpr int H = NV / 2;
+    const bool up = (lane & OFF) != 0;
+#pragma unroll
+    for (int m = 0; m < H; ++m) {
+      const double send = up ? v[m] : v[H + m], keep = up ? v[H + m] : v[m];
+      v[m] = keep + __shfl_xor(send, OFF, 64);
+    }
+    if (up) base += H;
+    return wave_totals<H, OFF / 2>(v, lane, base);
+  } else {
+#pragma unroll
+    for (int m = 0; m < NV; ++m) v[m] += __shfl_xor(v[m], OFF, 64);
+    return wave_totals<NV, OFF / 2>(v, lane, base);
+  }
+}
+
+// Blocks (point, group of DT detectors, part): each part sums a strided share
+// of the in-band bins into six complex FP64 partial sums per detector; the
+// chain kernel adds the parts in a fixed order (deterministic).
+//
+// Bound by vector instructions: 12 FP64 multiply-adds per bin and detector,
+// plus the phase.  A thread takes every detector of its group at a bin, so
+// that the template phase, the powers of b and the sample ramp k j*/N (cycles)
+// are formed once per bin; the ramp's numerator k j* mod N advances by a
+// constant from bin to bin (an add and a conditional subtract: exact for
+// every N).  4096 points of 4 x 131072 samples: 2.96 ms with one detector per
+// block, a 64-bit remainder and a division per bin and twelve tree sums;
+// 1.35 ms so (0.7 of the vector instruction rate).
+template <typename Real, int DT>
+__global__ void __launch_bounds__(kAdjThreads) k_adjoint_sums(const SegDesc* __restrict__ segs,
+                                                              const EvalDesc* __restrict__ evals,
+                                                              const int32_t* __restrict__ argmax, int n_det,
+                                                              int parts, double* __restrict__ sums) {
+  constexpr int NV = DT * kAdjSums * 2, NW = kAdjThreads / 64;
+  const int e = blockIdx.x, i0 = blockIdx.y * DT, part = blockIdx.z;
   const EvalDesc& ev = evals[e];
-  double* out = sums + (((int64_t)e * n_det + i) * parts + part) * kAdjSums * 2;
+  const int tid = threadIdx.x;
+  // sums[e][i][part][sum][re, im]
+  double* out = sums + ((int64_t)e * n_det * parts + part) * kAdjSums * 2;
+  const int nd = n_det - i0 < DT ? n_det - i0 : DT;   // detectors of this group (the last may hold fewer)
   if (ev.status != 1) {
-    if (threadIdx.x < kAdjSums * 2) out[threadIdx.x] = 0.0;
+    if (tid < nd * kAdjSums * 2) {
+      const int d = tid / (kAdjSums * 2);
+      out[(int64_t)(i0 + d) * parts * kAdjSums * 2 + tid - d * (kAdjSums * 2)] = 0.0;
+    }
     return;
   }
   const SegDesc& sg = segs[ev.seg];
   const int64_t N = sg.n;
   const int64_t jstar = argmax[e];
-  const cplx<Real>* y = (const cplx<Real>*)sg.y;
-  double acc[kAdjSums][2];
-  for (int m = 0; m < kAdjSums; ++m) acc[m][0] = acc[m][1] = 0.0;
-  for (int k = sg.k_lo + part * 256 + threadIdx.x; k <= sg.k_hi; k += 256 * parts) {
-    const int kk = k - sg.k_lo;
-    const double b = sg.b[kk];
-    const double phc = common_phase(ev.coef, b);
-    const double ramp = (double)(((int64_t)k * jstar) % N) / (double)N;
-    const double ph = (double)k * ev.dly[i] + phc + ramp;
-    const double r = ph - rint(ph);
-    Real sn, cs;
-    sincos_rev((Real)r, &sn, &cs);
-    const cplx<Real> a = mul(y[(int64_t)kk * n_det + i], mk<Real>(cs, sn));
-    const double ax = (double)a.x, ay = (double)a.y;
-    const double b2 = b * b, b3 = b2 * b, b5 = b3 * b2;
-    const double w[kAdjSums] = {1.0, b5, b3, b2, b, (double)k};
+  const cplx<Real>* y = (const cplx<Real>*)sg.y + i0;
+  const double* bt = sg.b;
+  const int k_lo = sg.k_lo, k_hi = sg.k_hi;
+  double dly[DT];
+  int at[DT];
 #pragma unroll
-    for (int m = 0; m < kAdjSums; ++m) {
-      acc[m][0] += w[m] * ax;
-      acc[m][1] += w[m] * ay;
+  for (int d = 0; d < DT; ++d) {
+    at[d] = d < nd ? d : 0;   // a missing detector repeats the first one's; its sums are not written
+    dly[d] = ev.dly[i0 + at[d]];
+  }
+  const double coef[4] = {ev.coef[0], ev.coef[1], ev.coef[2], ev.coef[3]};
+  const double inv_n = 1.0 / (double)N;
+  const int stride = kAdjThreads * parts;
+  int k = k_lo + part * kAdjThreads + tid;
+  uint32_t m = (uint32_t)(((int64_t)k * jstar) % N);
+  const uint32_t dm = (uint32_t)(((int64_t)stride * jstar) % N), nn = (uint32_t)N;
+  double acc[NV];
+#pragma unroll
+  for (int c = 0; c < NV; ++c) acc[c] = 0.0;
+  for (; k <= k_hi; k += stride) {
+    const int kk = k - k_lo;
+    const double b = bt[kk];
+    cplx<Real> yv[DT];
+#pragma unroll
+    for (int d = 0; d < DT; ++d) yv[d] = y[(int64_t)kk * n_det + at[d]];
+    const double phc = common_phase(coef, b);
+    const double ramp = (double)m * inv_n;
+    m += dm;
+    m = m >= nn ? m - nn : m;
+    const double b2 = b * b, b3 = b2 * b, b5 = b3 * b2;
+    const double kd = (double)k;
+#pragma unroll
+    for (int d = 0; d < DT; ++d) {
+      const double ph = kd * dly[d] + phc + ramp;
+      const double r = ph - rint(ph);
+      Real sn, cs;
+      sincos_rev((Real)r, &sn, &cs);
+      const cplx<Real> a = mul(yv[d], mk<Real>(cs, sn));
+      const double ax = (double)a.x, ay = (double)a.y;
+      double* s = acc + d * kAdjSums * 2;
+      s[0] += ax;
+      s[1] += ay;
+      s[2] += b5 * ax;
+      s[3] += b5 * ay;
+      s[4] += b3 * ax;
+      s[5] += b3 * ay;
+      s[6] += b2 * ax;
+      s[7] += b2 * ay;
+      s[8] += b * ax;
+      s[9] += b * ay;
+      s[10] += kd * ax;
+      s[11] += kd * ay;
     }
   }
-  __shared__ double red[256];
-  for (int m = 0; m < kAdjSums; ++m)
-    for (int c = 0; c < 2; ++c) {
-      red[threadIdx.x] = acc[m][c];
-      __syncthreads();
-      for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-      }
-      if (threadIdx.x == 0) out[m * 2 + c] = red[0];
-      __syncthreads();
-    }
+  __shared__ double red[NW][NV];
+  int base = 0;
+  const int held = wave_totals<NV, 32>(acc, tid & 63, base);
+  // lanes that hold the same totals write the same values
+  for (int c = 0; c < held; ++c) red[tid >> 6][base + c] = acc[c];
+  __syncthreads();
+  if (tid < nd * kAdjSums * 2) {
+    double t = red[0][tid];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) t += red[w][tid];
+    const int d = tid / (kAdjSums * 2);
+    out[(int64_t)(i0 + d) * parts * kAdjSums * 2 + tid - d * (kAdjSums * 2)] = t;
+  }
 }
 
 // d coef / d tau0, d coef / d tau1.5 for coef = f* (0.6 tau0, tau1, -1.5 tau1.5, 3 tau2).
@@ -86,121 +161,125 @@ __device__ void coef_derivatives(double tau0, double tau15, double fs, double dc
   }
 }
 
-// One 64-thread block per point: the threads add the parts of the six sums
-// (fixed order, deterministic), then thread 0 applies the chain rule in FP64.
-// Per-point work arrays live in LDS rather than in per-lane scratch.
+// One wavefront per point: its lanes add the parts of the six sums (fixed
+// order, deterministic), then apply the chain rule in FP64, lane 8 q + i
+// holding detector i for parameter q (alpha, delta, tau0, tau1.5); sums over
+// detectors are butterflies inside a group of 8 lanes.  Bound by the latency
+// of its dependent FP64 operations (8 points: 14 us when one thread did it).
 __global__ void __launch_bounds__(64) k_chain(const NetDesc* __restrict__ netp, const SegDesc* __restrict__ segs,
                                               const EvalDesc* __restrict__ evals, const double* __restrict__ theta,
                                               const double* __restrict__ sums, int parts, int n,
                                               double* __restrict__ grad) {
-  const int e = blockIdx.x;
+  const int e = blockIdx.x, lane = threadIdx.x;
   const NetDesc& net = *netp;
   const EvalDesc& ev = evals[e];
   double* g = grad + 4 * (int64_t)e;
   if (ev.status != 1) {
-    if (threadIdx.x < 4) g[threadIdx.x] = 0.0;
+    if (lane < 4) g[lane] = 0.0;
     return;
   }
   const int D = net.n_det;
+  const int q = (lane >> 3) & 3, i = lane & 7;   // lanes 32..63 repeat lanes 0..31
+  const bool on = i < D;
+  // everything that does not depend on the sums is read first
+  const SegDesc& sg = segs[ev.seg];
+  const double df = sg.df, sigma = on ? sg.sigma[i] : 0.0;
+  const double* th = theta + 4 * (int64_t)e;
+  const double alpha = th[0], delta = th[1], tau0 = th[2], tau15 = th[3];
+  const double q0 = on ? ev.q[i][0] : 0.0, q1 = on ? ev.q[i][1] : 0.0;
+  const double v0 = on ? ev.v[i][0] : 0.0, v1 = on ? ev.v[i][1] : 0.0;
+  const bool full = (ev.rank == 2);
+  double pos[3] = {0.0, 0.0, 0.0}, ten[3][3] = {};
+  if (on)
+    for (int a = 0; a < 3; ++a) {
+      pos[a] = net.pos[i][a];
+      for (int b = 0; b < 3; ++b) ten[a][b] = net.ten[i][a][b];
+    }
   __shared__ double S[kMaxDet * kAdjSums * 2];
-  for (int m = threadIdx.x; m < D * kAdjSums * 2; m += 64) {
-    const int i = m / (kAdjSums * 2), c = m - i * (kAdjSums * 2);
+  for (int m = lane; m < D * kAdjSums * 2; m += 64) {
+    const int d = m / (kAdjSums * 2), c = m - d * (kAdjSums * 2);
+    const double* s = sums + ((int64_t)e * D + d) * parts * kAdjSums * 2 + c;
     double t = 0.0;
-    for (int part = 0; part < parts; ++part) t += sums[(((int64_t)e * D + i) * parts + part) * kAdjSums * 2 + c];
+    // batches of eight loads in flight
+    int part = 0;
+    for (; part + 8 <= parts; part += 8) {
+      double u[8];
+#pragma unroll
+      for (int w = 0; w < 8; ++w) u[w] = s[(part + w) * kAdjSums * 2];
+      t += ((u[0] + u[1]) + (u[2] + u[3])) + ((u[4] + u[5]) + (u[6] + u[7]));
+    }
+    for (; part < parts; ++part) t += s[part * kAdjSums * 2];
     S[m] = t;
   }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  const SegDesc& sg = segs[ev.seg];
-  const double* th = theta + 4 * (int64_t)e;
-  const double alpha = th[0], delta = th[1];
-  double dc[2][4];
-  coef_derivatives(th[2], th[3], net.f_star, dc);
   double sa, ca, sd, cd;
   sincos(alpha, &sa, &ca);
   sincos(delta, &sd, &cd);
   const double ex[3] = {sa, -ca, 0.0}, ey[3] = {-sd * ca, -sd * sa, cd};
-  // derivatives of n, e_X = -alpha_hat, e_Y = delta_hat with respect to (alpha, delta)
-  const double dn[2][3] = {{-cd * sa, cd * ca, 0.0}, {-sd * ca, -sd * sa, cd}};
-  const double dex[2][3] = {{ca, sa, 0.0}, {0.0, 0.0, 0.0}};
-  const double dey[2][3] = {{sd * sa, -sd * ca, 0.0}, {-cd * ca, -cd * sa, -sd}};
-  __shared__ double dV[2][kMaxDet][2], ddl[2][kMaxDet];
-  __shared__ double zr[kMaxDet], zi[kMaxDet], pz_r[kMaxDet], pz_i[kMaxDet], rr[kMaxDet], ri[kMaxDet];
-  for (int i = 0; i < D; ++i) {
-    for (int q = 0; q < 2; ++q) {
-      const double* r = net.pos[i];
-      ddl[q][i] = -(dn[q][0] * r[0] + dn[q][1] * r[1] + dn[q][2] * r[2]) / kC * sg.df;
-      double up = 0.0, uc = 0.0;
-      for (int a = 0; a < 3; ++a)
-        for (int b = 0; b < 3; ++b) {
-          const double d = net.ten[i][a][b];
-          up += d * (dex[q][a] * ex[b] + ex[a] * dex[q][b] - dey[q][a] * ey[b] - ey[a] * dey[q][b]);
-          uc += d * (dex[q][a] * ey[b] + ex[a] * dey[q][b] + dey[q][a] * ex[b] + ey[a] * dex[q][b]);
-        }
-      dV[q][i][0] = sg.sigma[i] * up;
-      dV[q][i][1] = sg.sigma[i] * uc;
+  // derivatives of n, e_X = -alpha_hat, e_Y = delta_hat with respect to alpha (q = 0) or delta
+  const bool qa = (q == 0);
+  const double dn[3] = {qa ? -cd * sa : -sd * ca, qa ? cd * ca : -sd * sa, qa ? 0.0 : cd};
+  const double dex[3] = {qa ? ca : 0.0, qa ? sa : 0.0, 0.0};
+  const double dey[3] = {qa ? sd * sa : -cd * ca, qa ? -sd * ca : -cd * sa, qa ? 0.0 : -sd};
+  const double ddl = -(dn[0] * pos[0] + dn[1] * pos[1] + dn[2] * pos[2]) / kC * df;
+  double up = 0.0, uc = 0.0;
+  for (int a = 0; a < 3; ++a)
+    for (int b = 0; b < 3; ++b) {
+      const double d = ten[a][b];
+      up += d * (dex[a] * ex[b] + ex[a] * dex[b] - dey[a] * ey[b] - ey[a] * dey[b]);
+      uc += d * (dex[a] * ey[b] + ex[a] * dey[b] + dey[a] * ex[b] + ey[a] * dex[b]);
     }
-    zr[i] = S[(i * kAdjSums + 0) * 2];
-    zi[i] = S[(i * kAdjSums + 0) * 2 + 1];
-  }
+  const double dV0 = sigma * up, dV1 = sigma * uc;
+  double dc[2][4];
+  coef_derivatives(tau0, tau15, net.f_star, dc);
+  __syncthreads();   // S
+  double Si[kAdjSums * 2];
+  for (int c = 0; c < kAdjSums * 2; ++c) Si[c] = on ? S[i * kAdjSums * 2 + c] : 0.0;
+  auto sum8 = [](double x) {
+    x += __shfl_xor(x, 1, 8);
+    x += __shfl_xor(x, 2, 8);
+    x += __shfl_xor(x, 4, 8);
+    return x;
+  };
+  const double zr = Si[0], zi = Si[1];
   // P z = Q (Q^T z)
-  double c0r = 0, c0i = 0, c1r = 0, c1i = 0;
-  for (int i = 0; i < D; ++i) {
-    c0r += ev.q[i][0] * zr[i]; c0i += ev.q[i][0] * zi[i];
-    c1r += ev.q[i][1] * zr[i]; c1i += ev.q[i][1] * zi[i];
-  }
-  for (int i = 0; i < D; ++i) {
-    pz_r[i] = ev.q[i][0] * c0r + ev.q[i][1] * c1r;
-    pz_i[i] = ev.q[i][0] * c0i + ev.q[i][1] * c1i;
-  }
+  const double c0r = sum8(q0 * zr), c0i = sum8(q0 * zi), c1r = sum8(q1 * zr), c1i = sum8(q1 * zi);
+  const double pz_r = q0 * c0r + q1 * c1r, pz_i = q0 * c0i + q1 * c1i;
   // w = (V^T V)^-1 V^T z (rank two only), r = z - V w
-  double wr[2] = {0, 0}, wi[2] = {0, 0};
-  const bool full = (ev.rank == 2);
-  for (int i = 0; i < D; ++i) rr[i] = ri[i] = 0.0;
+  double wr0 = 0, wi0 = 0, wr1 = 0, wi1 = 0, rr = 0, ri = 0;
   if (full) {
-    double G00 = 0, G01 = 0, G11 = 0, br0 = 0, bi0 = 0, br1 = 0, bi1 = 0;
-    for (int i = 0; i < D; ++i) {
-      G00 += ev.v[i][0] * ev.v[i][0];
-      G01 += ev.v[i][0] * ev.v[i][1];
-      G11 += ev.v[i][1] * ev.v[i][1];
-      br0 += ev.v[i][0] * zr[i]; bi0 += ev.v[i][0] * zi[i];
-      br1 += ev.v[i][1] * zr[i]; bi1 += ev.v[i][1] * zi[i];
-    }
+    const double G00 = sum8(v0 * v0), G01 = sum8(v0 * v1), G11 = sum8(v1 * v1);
+    const double br0 = sum8(v0 * zr), bi0 = sum8(v0 * zi), br1 = sum8(v1 * zr), bi1 = sum8(v1 * zi);
     const double det = G00 * G11 - G01 * G01;
-    wr[0] = (G11 * br0 - G01 * br1) / det; wi[0] = (G11 * bi0 - G01 * bi1) / det;
-    wr[1] = (G00 * br1 - G01 * br0) / det; wi[1] = (G00 * bi1 - G01 * bi0) / det;
-    for (int i = 0; i < D; ++i) {
-      rr[i] = zr[i] - (ev.v[i][0] * wr[0] + ev.v[i][1] * wr[1]);
-      ri[i] = zi[i] - (ev.v[i][0] * wi[0] + ev.v[i][1] * wi[1]);
+    wr0 = (G11 * br0 - G01 * br1) / det; wi0 = (G11 * bi0 - G01 * bi1) / det;
+    wr1 = (G00 * br1 - G01 * br0) / det; wi1 = (G00 * bi1 - G01 * bi0) / det;
+    rr = zr - (v0 * wr0 + v1 * wr1);
+    ri = zi - (v0 * wi0 + v1 * wi1);
+  }
+  // d z^i = 2 pi i * s, s = sum_p dcoef_p S_p + ddly S_k
+  double sr = 0.0, si = 0.0;
+  if (q >= 2) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const double d = q == 2 ? dc[0][p] : dc[1][p];
+      sr += d * Si[(1 + p) * 2];
+      si += d * Si[(1 + p) * 2 + 1];
     }
+  } else {
+    sr = ddl * Si[10];
+    si = ddl * Si[11];
   }
   const double twopi = 2.0 * kPi;
-  for (int q = 0; q < 4; ++q) {
-    double acc = 0.0;
-    for (int i = 0; i < D; ++i) {
-      // d z^i = 2 pi i * s, s = sum_p dcoef_p S_p + ddly S_k
-      double sr = 0.0, si = 0.0;
-      if (q >= 2) {
-        for (int p = 0; p < 4; ++p) {
-          sr += dc[q - 2][p] * S[(i * kAdjSums + 1 + p) * 2];
-          si += dc[q - 2][p] * S[(i * kAdjSums + 1 + p) * 2 + 1];
-        }
-      } else {
-        sr = ddl[q][i] * S[(i * kAdjSums + 5) * 2];
-        si = ddl[q][i] * S[(i * kAdjSums + 5) * 2 + 1];
-      }
-      const double dzr = -twopi * si, dzi = twopi * sr;
-      // 2 Re(conj(Pz_i) dz_i)
-      acc += 2.0 * (pz_r[i] * dzr + pz_i[i] * dzi);
-      if (q < 2 && full) {
-        // 2 Re(conj(r_i) (dV_i0 w_0 + dV_i1 w_1))
-        const double tr = dV[q][i][0] * wr[0] + dV[q][i][1] * wr[1];
-        const double ti = dV[q][i][0] * wi[0] + dV[q][i][1] * wi[1];
-        acc += 2.0 * (rr[i] * tr + ri[i] * ti);
-      }
-    }
-    g[q] = acc;
+  const double dzr = -twopi * si, dzi = twopi * sr;
+  // 2 Re(conj(Pz_i) dz_i)
+  double acc = 2.0 * (pz_r * dzr + pz_i * dzi);
+  if (q < 2 && full) {
+    // 2 Re(conj(r_i) (dV_i0 w_0 + dV_i1 w_1))
+    const double tr = dV0 * wr0 + dV1 * wr1;
+    const double ti = dV0 * wi0 + dV1 * wi1;
+    acc += 2.0 * (rr * tr + ri * ti);
   }
+  acc = sum8(acc);
+  if (lane < 32 && i == 0) g[q] = acc;
 }
 
 // Polish trials: theta_t = theta + step_frac 2^-t w^2 g / |w g|, t = 0..T-1
@@ -266,17 +345,22 @@ hipError_t launch_polish_select(double* theta, double* fitness, int32_t* argmax,
   return hipGetLastError();
 }
 
+// Detectors per adjoint block: every detector up to four (24 registers of
+// sums each), networks of five to eight in two groups.
+static int adj_group(int n_det) { return n_det <= 4 ? n_det : (n_det + 1) / 2; }
+
 int grad_parts(int n, int n_det) {
   // enough blocks to cover the chip for small batches, one part for large ones
-  int parts = (kAdjMinBlocks + n * n_det - 1) / (n * n_det);
+  const int groups = n_det <= 4 ? 1 : 2;
+  int parts = (kAdjMinBlocks + n * groups - 1) / (n * groups);
   return parts < 1 ? 1 : (parts > kAdjMaxParts ? kAdjMaxParts : parts);
 }
 
 int alloc_grad_buffers(GradBuffers& g, int max_batch, int n_det) {
   g.max_batch = max_batch;
   g.n_det = n_det;
-  // n * n_det * parts <= n * n_det + kAdjMinBlocks for every n
-  const size_t entries = (size_t)max_batch * n_det + kAdjMinBlocks + kAdjMaxParts;
+  // n * parts <= n + kAdjMinBlocks for every n
+  const size_t entries = ((size_t)max_batch + kAdjMinBlocks) * n_det;
   const size_t bytes = entries * kAdjSums * 2 * sizeof(double);
   if (hipMalloc((void**)&g.sums, bytes) != hipSuccess) {
     g.sums = nullptr;
@@ -294,11 +378,26 @@ hipError_t launch_gradient(int precision, const GradBuffers& g, const NetDesc* n
                            const EvalDesc* evals, const double* theta, const int32_t* argmax, int n, int n_det,
                            double* grad, hipStream_t s) {
   const int parts = grad_parts(n, n_det);
-  const dim3 grid(n, n_det, parts);
-  if (precision == 0)
-    hipLaunchKernelGGL(k_adjoint_sums<float>, grid, dim3(256), 0, s, segs, evals, argmax, n_det, parts, g.sums);
-  else
-    hipLaunchKernelGGL(k_adjoint_sums<double>, grid, dim3(256), 0, s, segs, evals, argmax, n_det, parts, g.sums);
+  const int dt = adj_group(n_det);
+  const dim3 grid(n, (n_det + dt - 1) / dt, parts), block(kAdjThreads);
+#define FCAS_ADJOINT(DT)                                                                                    \
+  case DT:                                                                                                  \
+    if (precision == 0)                                                                                     \
+      hipLaunchKernelGGL((k_adjoint_sums<float, DT>), grid, block, 0, s, segs, evals, argmax, n_det, parts, \
+                         g.sums);                                                                           \
+    else                                                                                                    \
+      hipLaunchKernelGGL((k_adjoint_sums<double, DT>), grid, block, 0, s, segs, evals, argmax, n_det, parts, \
+                         g.sums);                                                                           \
+    break;
+  switch (dt) {
+    FCAS_ADJOINT(1)
+    FCAS_ADJOINT(2)
+    FCAS_ADJOINT(3)
+    FCAS_ADJOINT(4)
+    default:
+      return hipErrorInvalidValue;
+  }
+#undef FCAS_ADJOINT
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_chain, dim3(n), dim3(64), 0, s, net, segs, evals, theta, g.sums, parts, n, grad);

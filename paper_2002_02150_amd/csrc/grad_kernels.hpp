@@ -10,7 +10,8 @@ namespace fcas {
 // Per point and detector, six complex sums over the in-band bins at j*:
 // [0] z^i, [1..4] sum a_k b_k^{5,3,2,1}, [5] sum a_k k.
 constexpr int kAdjSums = 6;
-constexpr int kAdjMinBlocks = 2048;   // adjoint blocks wanted for small batches
+constexpr int kAdjThreads = 256;      // threads of an adjoint block
+constexpr int kAdjMinBlocks = 1024;   // adjoint blocks wanted for small batches
 constexpr int kAdjMaxParts = 64;      // most parts one (point, detector) sum is split into
 
 struct GradBuffers {
