@@ -180,7 +180,7 @@ int fitness_eval_batch(fcas_ctx* ctx, int32_t n, const double* d_theta, const in
  * array of 64 MiB that the library holds on each GPU it runs on until the
  * process ends, instead of the context's buffers.  The call allocates nothing.
  * Limit: the tables take about 0.75 KB + 8 S bytes per point (S = pass-2
- * partials per point: at most 512 for contexts whose max_samples is at most
+ * partials per point: at most 128 for contexts whose max_samples is at most
  * 262144) and the rest is FFT workspace, which must hold at least one point of
  * the longest registered segment (2 N 8 bytes mixed, 2 N 16 bytes FP64: an
  * hour-long segment does not fit); more points than it holds run in chunks.  A call

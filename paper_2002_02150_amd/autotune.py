@@ -4,11 +4,13 @@ fastest choice per length to tuning.json (applied by Context by default).
 
     python -m paper_2002_02150_amd.autotune [--lengths 131072,262144] [--out PATH]
 
-Timing: fitness batches of `batch` points spread over the search rectangle
+Timing: fitness batches of `batches` points spread over the search rectangle
 (every point evaluated; 256 by default, between the 192 points a 320-particle
 swarm keeps inside the rectangle early in a search and the 311 it keeps at the
-end), HIP events around `reps` back-to-back calls, best of three such runs.  The data are random: the cost of an evaluation does not depend
-on the data values.
+end, and 16, a small call), HIP events around `reps` back-to-back calls, best
+of three such runs; a choice is ranked by the geometric mean over the batches.
+The data are random: the cost of an evaluation does not depend on the data
+values.
 """
 from __future__ import annotations
 
@@ -23,8 +25,11 @@ import torch
 
 from . import fcas
 
-DEFAULT_LENGTHS = (8192, 65536, 131072, 196608, 262144, 460800, 3686400, 7372800)
-GRIDS = (1024, 2048, 4096)
+DEFAULT_LENGTHS = (2048, 4096, 8192, 16384, 24576, 32768, 49152, 65536, 98304, 131072, 196608, 262144, 460800,
+                   3686400, 7372800)
+# persistent work-groups of the first pass, and of the last (and middle) one
+GRIDS1 = (512, 1024, 2048)
+GRIDS2 = (2048, 4096, 16384)
 # rectangle of component masses in [1, 3] Msun at f_low = 30 Hz
 BOX_LO = (0.0, -math.pi / 2, 15.0336, 0.841913)
 BOX_HI = (2.0 * math.pi, math.pi / 2, 93.8141, 1.75126)
@@ -66,12 +71,13 @@ def time_plan(ctx, plan, g1, g2, xf, psd, theta, seg, reps):
     return min(samples)
 
 
-def autotune(lengths=DEFAULT_LENGTHS, n_det=4, fs=2048.0, batch=256, reps=10, grids=GRIDS, out=fcas.TUNING_PATH,
-             device=0, log=print):
+def autotune(lengths=DEFAULT_LENGTHS, n_det=4, fs=2048.0, batches=(16, 256), reps=10, grids1=GRIDS1, grids2=GRIDS2,
+             out=fcas.TUNING_PATH, device=0, log=print):
     dev = torch.device("cuda", device)
     pos, ten = _network(n_det, dev)
     gen = torch.Generator(device="cpu").manual_seed(1234)
     results, choices = [], {}
+    batch = max(batches)
     for n in lengths:
         cands = [p for p, d in fcas.plans() if d["n"] == n]
         if not cands:
@@ -91,18 +97,19 @@ def autotune(lengths=DEFAULT_LENGTHS, n_det=4, fs=2048.0, batch=256, reps=10, gr
                            max_batch=batch, max_samples=n, device=device, tuning=None, workspace_bytes=ws)
         best = None
         for p in cands:
-            for g1 in grids:
-                for g2 in grids:
-                    ms = time_plan(ctx, p, g1, g2, xf, psd, theta, seg, reps)
-                    results.append(dict(n=n, plan=p, grid1=g1, grid2=g2, ms=ms))
+            for g1 in grids1:
+                for g2 in grids2:
+                    each = [time_plan(ctx, p, g1, g2, xf, psd, theta[:m], seg[:m], reps) for m in batches]
+                    ms = math.exp(sum(math.log(t) for t in each) / len(each))
+                    results.append(dict(n=n, plan=p, grid1=g1, grid2=g2, ms=ms, each=each))
                     if best is None or ms < best["ms"]:
                         best = dict(plan=p, grid1=g1, grid2=g2, ms=ms)
             log(f"N={n} plan {p}: best so far {best}")
         ctx.close()
         choices[str(n)] = best
         log(f"N={n}: chose {best}")
-    doc = dict(device=torch.cuda.get_device_name(dev), n_det=n_det, batch=batch, reps=reps,
-               what="mean device time of one fitness call (set-up, passes, finalize)",
+    doc = dict(device=torch.cuda.get_device_name(dev), n_det=n_det, batches=list(batches), reps=reps,
+               what="mean device time of one fitness call (set-up, passes, finalize), geometric mean over the batches",
                written=time.strftime("%Y-%m-%d %H:%M:%S"), choices=choices, measurements=results)
     if out:
         with open(out, "w") as fh:

@@ -14,7 +14,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libfcas.so")
 BUILD = os.path.join(HERE, "_build")
-SOURCES = ["fcas_api.cpp", "setup.hip", "eval_f32.hip", "eval_f64.hip", "grad.hip", "pso.hip", "inject.hip", "tail.hip"]
+SOURCES = ["eval_f32.hip", "eval_f64.hip", "fcas_api.cpp", "setup.hip", "grad.hip", "pso.hip", "inject.hip", "tail.hip"]
+# pass 1, one object per precision and detector count (compiled in parallel)
+PASS1 = [("eval_pass1.hip", real, dt) for dt in range(8, 0, -1) for real in ("float", "double")]
 ARCH = os.environ.get("FCAS_OFFLOAD_ARCH", "gfx950")
 
 
@@ -36,10 +38,15 @@ def common_flags():
             "-Wall", "-Wno-unused-function", "-Wno-unused-variable", "-Wno-unused-value", "-Wno-unused-result"]
 
 
-def compile_one(src):
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
+def compile_one(unit):
+    """unit: a source file, or (source file, FCAS_REAL, FCAS_DT)."""
+    src, defs, suffix = unit, [], ""
+    if isinstance(unit, tuple):
+        src, real, dt = unit
+        defs, suffix = [f"-DFCAS_REAL={real}", f"-DFCAS_DT={dt}"], f"_{real}_{dt}"
+    obj = os.path.join(BUILD, os.path.splitext(src)[0] + suffix + ".o")
     lang = ["-x", "hip"] if src.endswith(".cpp") else []
-    cmd = [hipcc()] + common_flags() + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [hipcc()] + common_flags() + defs + lang + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
@@ -48,8 +55,9 @@ def compile_one(src):
 
 def build(verbose=True):
     os.makedirs(BUILD, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 4)) as ex:
-        objs = list(ex.map(compile_one, SOURCES))
+    units = SOURCES[:2] + PASS1 + SOURCES[2:]   # the longest first
+    with ThreadPoolExecutor(max_workers=min(len(units), os.cpu_count() or 4)) as ex:
+        objs = list(ex.map(compile_one, units))
     tmp = OUT + ".tmp"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -4,22 +4,15 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "fitness_tiles.hpp"
 #include "plans.hpp"
 
-// Build-time overrides of the pass kernels' settings (-1: the per-plan
-// choice of PassTune below): software prefetch of the next work item's data
-// (1) or a fetch at the start of each item (0), and the occupancy each pass
-// kernel is compiled for (waves per SIMD; 1 = no bound below the register
-// file's).
-#ifndef FCAS_PASS1_PREFETCH
-#define FCAS_PASS1_PREFETCH (-1)
-#endif
+// Build-time overrides of the occupancy each pass kernel is compiled for
+// (waves per SIMD; -1: the per-plan choice of PassTune below).
 #ifndef FCAS_PASS1_WAVES
 #define FCAS_PASS1_WAVES (-1)
-#endif
-#ifndef FCAS_PASS2_PREFETCH
-#define FCAS_PASS2_PREFETCH (-1)
 #endif
 #ifndef FCAS_PASS2_WAVES
 #define FCAS_PASS2_WAVES (-1)
@@ -27,20 +20,26 @@
 
 namespace fcas {
 
-// Settings of the pass kernels of one plan.  Float transforms of 8-element
-// threads fit in 128 VGPRs without a prefetch register set: at 4 waves per
-// SIMD (their LDS allows 4 work-groups of 4 waves per CU) they run faster
-// than at 3 waves with the next item prefetched (measured on the 4 x 131072
-// search: pass 1 -7%, pass 2 -10%); the other plans (16-element threads,
-// double precision) keep the prefetch at their register-bound occupancy.
-template <typename Real, class PL>
+// Settings of the pass kernels of one plan.
+//   joint: both series of a transform exchange through LDS in one step (two
+//   buffers, half the synchronisations), else one after the other through one
+//   buffer, the first stored before the second's stages begin, which takes
+//   half the LDS and, in pass 1, leaves the second series in its half-full
+//   input registers meanwhile.
+//   waves: occupancy the kernel is compiled for (waves per SIMD).
+// Float transforms of 8-element threads fit in 128 VGPRs: 4 waves; pass 1 of
+// 12 or 16 elements with its data kept takes 190-210 (320 points of 196608 in
+// 192-point columns: 199 us at 2 waves, 212 at 3 with spills).
+//   keep: pass 1 holds a tile's segment data in registers from point to point
+//   (where they leave room for the transform), else it reads them again.
+template <typename Real, class PL, int DT = 1>
 struct PassTune {
-  static constexpr bool light1 = sizeof(Real) == 4 && PL::E1 == 8;
-  static constexpr bool light2 = sizeof(Real) == 4 && PL::E2 == 8;
-  static constexpr bool prefetch1 = FCAS_PASS1_PREFETCH >= 0 ? FCAS_PASS1_PREFETCH != 0 : !light1;
-  static constexpr bool prefetch2 = FCAS_PASS2_PREFETCH >= 0 ? FCAS_PASS2_PREFETCH != 0 : !light2;
-  static constexpr int waves1 = FCAS_PASS1_WAVES >= 0 ? FCAS_PASS1_WAVES : (light1 ? 4 : 3);
-  static constexpr int waves2 = FCAS_PASS2_WAVES >= 0 ? FCAS_PASS2_WAVES : (light2 ? 4 : 1);
+  static constexpr bool f32 = sizeof(Real) == 4;
+  static constexpr bool joint1 = f32 && PL::E1 <= 12, joint2 = f32 && PL::E2 <= 12;
+  static constexpr int data1 = (DT * 2 * (int)sizeof(Real) / 4 + 2) * (PL::E1 / 2);   // registers of the segment data
+  static constexpr bool keep = data1 <= (f32 && PL::E1 > 8 ? 80 : 40);
+  static constexpr int waves1 = FCAS_PASS1_WAVES >= 0 ? FCAS_PASS1_WAVES : !f32 ? 3 : PL::E1 == 8 ? 4 : 2;
+  static constexpr int waves2 = FCAS_PASS2_WAVES >= 0 ? FCAS_PASS2_WAVES : (f32 && PL::E2 == 8 ? 4 : 3);
 };
 
 struct PassArgs {
@@ -52,6 +51,7 @@ struct PassArgs {
   void* part_g;            // [max_batch][part_stride] partial maxima (Real)
   int32_t* part_j;         // [max_batch][part_stride] their samples
   int32_t part_stride;     // partials per evaluation slot (>= the plan's PARTS2)
+  int32_t nt;              // non-temporal pass-1 stores
   int32_t n_det;
   int32_t chunk_begin;     // first list position handled by this launch
   int32_t cap;             // workspace slots (positions per launch)
@@ -86,19 +86,11 @@ __device__ __forceinline__ void lds_exchange_sync() {
   }
 }
 
-// Float transforms exchange both series in one step (LDS buffers buf0 and
-// buf1, two synchronisations per stage); double transforms take turns in buf0,
-// keeping their LDS within 64 KiB per work-group.
-template <typename Real>
-constexpr bool kJointExchange = sizeof(Real) == 4;
-template <typename Real>
-constexpr int kLdsSeries = kJointExchange<Real> ? 2 : 1;
-
 // All stages of the S series (1 or 2) of one transform held in registers;
 // JOINT: two series exchange through LDS together (buf0, buf1), else they take
 // turns in buf0.
 template <typename Real, class PL, int L, int E, class Rad, int I, int Ns, bool HALF, bool WAVE, int PAD,
-          bool JOINT = kJointExchange<Real>, int S = 2>
+          bool JOINT, int S>
 __device__ __forceinline__ void run_stages(cplx<Real> (&v)[S][E], cplx<Real>* buf0, cplx<Real>* buf1,
                                            const cplx<Real>* tw, int t) {
   if constexpr (I < Rad::count) {
@@ -125,38 +117,98 @@ __device__ __forceinline__ void run_stages(cplx<Real> (&v)[S][E], cplx<Real>* bu
         }
       }
     }
-    run_stages<Real, PL, L, E, Rad, I + 1, Ns * R, false, WAVE, PAD, JOINT>(v, buf0, buf1, tw, t);
+    run_stages<Real, PL, L, E, Rad, I + 1, Ns * R, false, WAVE, PAD, JOINT, S>(v, buf0, buf1, tw, t);
   }
 }
 
-// Pass-1 work item -> (list position in the launch, column tile).  Point-major
-// (every tile of one point, then the next point) for two-pass plans, whose
-// segment data stay in the L2 anyway; tile-major for the long three-pass
-// segments (112 MB of data at one hour), so that the work-groups in flight
-// take one tile of many points and share its data in the cache instead of
-// each point re-reading the whole segment from HBM.  Work-groups are handed
-// to the 8 XCDs in turn, so with a grid that is a multiple of 8, items that
-// agree mod 8 run on one XCD: the tile-major order then gives XCD x the tiles
-// x, x + 8, ... (when 8 divides TILES1), and each XCD's L2 fetches an eighth
-// of the segment instead of all of it (pass 1 3% faster at one hour).  Any
-// grid gives the same results: only the order of the items changes.
-template <class PL>
-constexpr bool kTileMajor1 = PL::THREE;
-
-template <class PL>
-__device__ __forceinline__ void pass1_decode(int item, int span, int& slot, int& tile) {
-  if constexpr (kTileMajor1<PL> && PL::TILES1 % 8 == 0) {
-    const int x = item & 7, r = item >> 3;
-    const int g = r / span;
-    slot = r - g * span;
-    tile = x + 8 * g;
-  } else if constexpr (kTileMajor1<PL>) {
-    tile = item / span;
-    slot = item - tile * span;
-  } else {
-    slot = item / PL::TILES1;
-    tile = item - slot * PL::TILES1;
+// The stages of passes 1 and 2, with their factors in registers: of one
+// series, or of both exchanging together.
+template <typename Real, int L, int E, class Rad, int I, bool SHIFT, bool HALF, bool WAVE, int PAD>
+__device__ __forceinline__ void run_geo_series(cplx<Real> (&v)[E], cplx<Real>* buf,
+                                               const GeoSet<Real, L, E, Rad, SHIFT>& g, int t) {
+  if constexpr (I < Rad::count) {
+    geo_stage<Real, L, E, Rad, I, SHIFT, HALF && I == 0, PAD>(v, buf, g, t);
+    if constexpr (I < Rad::count - 1) {
+      lds_exchange_sync<WAVE>();
+      stage_gather<Real, L, E, PAD>(v, buf, t);
+      lds_exchange_sync<WAVE>();
+    }
+    run_geo_series<Real, L, E, Rad, I + 1, SHIFT, HALF, WAVE, PAD>(v, buf, g, t);
   }
+}
+
+template <typename Real, int L, int E, class Rad, int I, bool SHIFT, bool HALF, bool WAVE, int PAD>
+__device__ __forceinline__ void run_geo_joint(cplx<Real> (&v)[2][E], cplx<Real>* buf0, cplx<Real>* buf1,
+                                              const GeoSet<Real, L, E, Rad, SHIFT>& g, int t) {
+  if constexpr (I < Rad::count) {
+    geo_stage<Real, L, E, Rad, I, SHIFT, HALF && I == 0, PAD>(v[0], buf0, g, t);
+    geo_stage<Real, L, E, Rad, I, SHIFT, HALF && I == 0, PAD>(v[1], buf1, g, t);
+    if constexpr (I < Rad::count - 1) {
+      lds_exchange_sync<WAVE>();
+      stage_gather<Real, L, E, PAD>(v[0], buf0, t);
+      stage_gather<Real, L, E, PAD>(v[1], buf1, t);
+      lds_exchange_sync<WAVE>();
+    }
+    run_geo_joint<Real, L, E, Rad, I + 1, SHIFT, HALF, WAVE, PAD>(v, buf0, buf1, g, t);
+  }
+}
+
+// Pass 1 of one item from its prologue's values to the workspace slot `out`.
+template <typename Real, class PL>
+using Pass1Geo = GeoSet<Real, PL::N1, PL::E1, typename PL::Rad1, false>;
+template <typename Real, class PL, bool NT>
+__device__ __forceinline__ void pass1_transform(cplx<Real> (&v)[2][PL::E1], cplx<Real>* out, cplx<Real>* buf0,
+                                                cplx<Real>* buf1, const Pass1Geo<Real, PL>& g, int tile, int c,
+                                                int p) {
+  using Rad = typename PL::Rad1;
+  if constexpr (PassTune<Real, PL>::joint1) {
+    run_geo_joint<Real, PL::N1, PL::E1, Rad, 0, false, true, false, kPad1>(v, buf0, buf1, g, p);
+    pass1_store<Real, PL, NT>(v, out, tile, c, p);
+  } else {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      run_geo_series<Real, PL::N1, PL::E1, Rad, 0, false, true, false, kPad1>(v[s], buf0, g, p);
+      pass1_store_series<Real, PL, NT>(v[s], out, s, tile, c, p);
+    }
+  }
+}
+
+// Pass 2 of one item from its rows: Gamma^2 of the thread's samples.
+template <class PL>
+constexpr bool kRowInWave = (64 % PL::P2) == 0;
+template <typename Real, class PL>
+using Pass2Geo = GeoSet<Real, PL::N2, PL::E2, typename PL::Rad2, !PL::THREE>;
+template <typename Real, class PL, bool WAVE>
+__device__ __forceinline__ void pass2_transform(cplx<Real> (&v)[2][PL::E2], Real (&g)[PL::E2], cplx<Real>* buf0,
+                                                cplx<Real>* buf1, const Pass2Geo<Real, PL>& geo, int p) {
+  using Rad = typename PL::Rad2;
+  if constexpr (PassTune<Real, PL>::joint2) {
+    run_geo_joint<Real, PL::N2, PL::E2, Rad, 0, !PL::THREE, false, WAVE, kPad2>(v, buf0, buf1, geo, p);
+#pragma unroll
+    for (int q = 0; q < PL::E2; ++q) g[q] = norm2(v[0][q]) + norm2(v[1][q]);
+  } else {
+    run_geo_series<Real, PL::N2, PL::E2, Rad, 0, !PL::THREE, false, WAVE, kPad2>(v[0], buf0, geo, p);
+#pragma unroll
+    for (int q = 0; q < PL::E2; ++q) g[q] = norm2(v[0][q]);
+    run_geo_series<Real, PL::N2, PL::E2, Rad, 0, !PL::THREE, false, WAVE, kPad2>(v[1], buf0, geo, p);
+#pragma unroll
+    for (int q = 0; q < PL::E2; ++q) g[q] = g[q] + norm2(v[1][q]);
+  }
+}
+
+// Work of passes 1 and 2: work-group b of a grid of TILES * G takes one tile
+// of every G-th point of the launch, so what belongs to the tile (its segment
+// data, twiddle factors, addresses) stays in registers from point to point,
+// while the work-groups of a group, which start together, are on the tiles of
+// one point at a time: their stores and loads cover whole rows of the
+// workspace between them (with the points of a tile in one work-group after
+// the other instead, pass 1 of 131072 lost what the fewer instructions gave,
+// and 262144, with 64-byte row pieces, 15%).
+template <int TILES>
+__device__ __forceinline__ void tile_of_block(int block, int nblocks, int& tile, int& first, int& step) {
+  tile = block % TILES;
+  first = block / TILES;
+  step = nblocks / TILES;
 }
 
 // Point (evaluation index) at list position `pos` of the launch, and its
@@ -168,80 +220,48 @@ __device__ __forceinline__ SegDesc segment_of(const PassArgs& a, int e) {
   return *const_view(a.segs + seg);
 }
 
-template <typename Real, class PL, int DT>
-__device__ __forceinline__ void pass1_fetch_item(Pass1Data<Real, PL, DT>& d, const PassArgs& a, int item, int span,
-                                                 int c, int p) {
-  int slot, tile;
-  pass1_decode<PL>(item, span, slot, tile);
-  const SegDesc sg = segment_of(a, list_entry(a, a.chunk_begin + slot));
-  pass1_fetch<Real, PL, DT>(d, sg, tile, c, p);
-}
-
 // LDS exchange buffers of the two passes: padded length of one transform and
 // elements per work-group.
 template <typename Real, class PL>
 struct PassLds {
   static constexpr int LP1 = lds_padded_len<kPad1>(PL::N1), LP2 = lds_padded_len<kPad2>(PL::N2);
-  static constexpr int X1 = kLdsSeries<Real> * PL::C * LP1, X2 = kLdsSeries<Real> * PL::RW * LP2;
+  static constexpr int X1 = (PassTune<Real, PL>::joint1 ? 2 : 1) * PL::C * LP1;
+  static constexpr int X2 = (PassTune<Real, PL>::joint2 ? 2 : 1) * PL::RW * LP2;
 };
 
-// Pass 1 on the items of `a` taken by work-group `block` of `nblocks`
-// (tw holds the length-N1 twiddles).
+// Pass 1 on the share of work-group `block` of `nblocks`.  The segment data of
+// the tile are read when the segment changes and stay in registers for the
+// points that follow.
 template <typename Real, class PL, int DT>
-__device__ __forceinline__ void pass1_body(const PassArgs& a, cplx<Real>* lds, const cplx<Real>* tw, int block,
-                                           int nblocks) {
+__device__ __forceinline__ void pass1_body(const PassArgs& a, cplx<Real>* lds, int block, int nblocks) {
   constexpr int LP = PassLds<Real, PL>::LP1;
   const int tid = threadIdx.x;
   const int span = launch_span(a);
-  const int items = span * PL::TILES1;
+  int tile, slot, step;
+  tile_of_block<PL::TILES1>(block, nblocks, tile, slot, step);
+  if (slot >= span) return;
   const int c = tid % PL::C, p = tid / PL::C;
   cplx<Real>* buf0 = lds + c * LP;
-  cplx<Real>* buf1 = kJointExchange<Real> ? lds + (PL::C + c) * LP : buf0;
-  if constexpr (DT > 0 && !PassTune<Real, PL>::prefetch1) {
-    // each item fetches its own segment data; other waves cover the latency
-    for (int item = block; item < items; item += nblocks) {
-      int slot, tile;
-      pass1_decode<PL>(item, span, slot, tile);
-      Pass1Data<Real, PL, DT> d;
-      pass1_fetch_item<Real, PL, DT>(d, a, item, span, c, p);
-      cplx<Real> v[2][PL::E1];
-      pass1_compute<Real, PL, DT>(v, d, pass1_point<Real, DT>(const_view(a.evals + list_entry(a, a.chunk_begin + slot))));
-      run_stages<Real, PL, PL::N1, PL::E1, typename PL::Rad1, 0, 1, true, false, kPad1>(v, buf0, buf1, tw, p);
-      pass1_store<Real, PL>(v, (cplx<Real>*)a.ws + (int64_t)slot * 2 * PL::N, tile, c, p);
+  cplx<Real>* buf1 = PassTune<Real, PL>::joint1 ? lds + (PL::C + c) * LP : buf0;
+  int cur_seg = -1;
+  Pass1Data<Real, PL, DT> d;
+  Pass1Geo<Real, PL> g;
+  g.init(p);
+  for (; slot < span; slot += step) {
+    const int e = list_entry(a, a.chunk_begin + slot);
+    const int seg = const_view(a.evals + e)->seg;
+    if (!PassTune<Real, PL, DT>::keep || seg != cur_seg) {
+      const SegDesc sg = *const_view(a.segs + seg);
+      pass1_fetch<Real, PL, DT>(d, sg, tile, c, p);
+      cur_seg = seg;
     }
-  } else if constexpr (DT > 0) {
-    // software pipeline: once an item's prologue has consumed its segment
-    // data, the next item's are fetched while this one is transformed (one set
-    // of prefetch registers)
-    Pass1Data<Real, PL, DT> d;
-    int item = block;
-    if (item < items) pass1_fetch_item<Real, PL, DT>(d, a, item, span, c, p);
-    for (; item < items; item += nblocks) {
-      int slot, tile;
-      pass1_decode<PL>(item, span, slot, tile);
-      cplx<Real> v[2][PL::E1];
-      pass1_compute<Real, PL, DT>(v, d, pass1_point<Real, DT>(const_view(a.evals + list_entry(a, a.chunk_begin + slot))));
-      // the fetch is unconditional (the last item re-reads its own data) so
-      // that every path through the loop has the same loads in flight and the
-      // compiler's wait counts never drain the prefetch early
-      const int next = item + nblocks;
-      pass1_fetch_item<Real, PL, DT>(d, a, next < items ? next : item, span, c, p);
-      run_stages<Real, PL, PL::N1, PL::E1, typename PL::Rad1, 0, 1, true, false, kPad1>(v, buf0, buf1, tw, p);
-      pass1_store<Real, PL>(v, (cplx<Real>*)a.ws + (int64_t)slot * 2 * PL::N, tile, c, p);
-    }
-  } else {
-    for (int item = block; item < items; item += nblocks) {
-      int slot, tile;
-      pass1_decode<PL>(item, span, slot, tile);
-      const int e = a.list[a.chunk_begin + slot];
-      const EvalDesc& ev = a.evals[e];
-      const SegDesc& sg = a.segs[ev.seg];
-      cplx<Real> v[2][PL::E1];
-      pass1_prologue<Real, PL, 0>(v, ev, sg, a.n_det, tile, c, p);
-      run_stages<Real, PL, PL::N1, PL::E1, typename PL::Rad1, 0, 1, true, false, kPad1>(v, buf0, buf1, tw, p);
-      cplx<Real>* ws = (cplx<Real>*)a.ws + (int64_t)slot * 2 * PL::N;
-      pass1_store<Real, PL>(v, ws, tile, c, p);
-    }
+    cplx<Real> v[2][PL::E1];
+    pass1_compute<Real, PL, DT>(v, d, pass1_point<Real, DT>(const_view(a.evals + e)));
+    cplx<Real>* out = (cplx<Real>*)a.ws + (int64_t)slot * 2 * PL::N;
+    if (a.nt)
+      pass1_transform<Real, PL, true>(v, out, buf0, buf1, g, tile, c, p);
+    else
+      pass1_transform<Real, PL, false>(v, out, buf0, buf1, g, tile, c, p);
   }
 }
 
@@ -253,11 +273,9 @@ __device__ __forceinline__ void init_twiddles(cplx<Real>* tw) {
 
 template <typename Real, class PL, int DT>
 __global__ void __launch_bounds__(PL::T1)
-    __attribute__((amdgpu_waves_per_eu(PassTune<Real, PL>::waves1))) k_pass1(PassArgs a) {
+    __attribute__((amdgpu_waves_per_eu(PassTune<Real, PL, DT>::waves1))) k_pass1(PassArgs a) {
   __shared__ cplx<Real> lds[PassLds<Real, PL>::X1];
-  __shared__ cplx<Real> tw[PL::N1];
-  init_twiddles<Real, PL::N1, PL::T1>(tw);
-  pass1_body<Real, PL, DT>(a, lds, tw, blockIdx.x, gridDim.x);
+  pass1_body<Real, PL, DT>(a, lds, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -276,7 +294,7 @@ constexpr bool kPassmJoint = false;
 constexpr int kPassmSeries = 2;         // series per work item (1: each series its own item)
 constexpr bool kPassmPrefetch = false;
 template <typename Real>
-constexpr bool kPassmJointFor = kPassmJoint && kJointExchange<Real> && kPassmSeries == 2;
+constexpr bool kPassmJointFor = kPassmJoint && sizeof(Real) == 4 && kPassmSeries == 2;
 
 // Work item -> (list position in the launch, first series, tile); the items
 // of one point run series by series, tiles in order.
@@ -304,7 +322,8 @@ __device__ __forceinline__ void passm_item(cplx<Real> (&v)[kPassmSeries][PL::EM]
   int slot, s0, tile;
   passm_decode<PL>(item, slot, s0, tile);
   passm_twiddle_in<Real, PL>(v, tile, c, p);
-  run_stages<Real, PL, PL::NM, PL::EM, typename PL::RadM, 0, 1, false, false, kPadM, kPassmJointFor<Real>>(
+  run_stages<Real, PL, PL::NM, PL::EM, typename PL::RadM, 0, 1, false, false, kPadM, kPassmJointFor<Real>,
+             kPassmSeries>(
       v, buf0, buf1, tw, p);
   passm_twiddle_out<Real, PL>(v, tile, c, p);
   passm_store<Real, PL>(v, (cplx<Real>*)a.ws + (int64_t)slot * 2 * PL::N, tile, c, p, s0);
@@ -360,23 +379,60 @@ __global__ void __launch_bounds__(PL::TM) k_passm(PassArgs a) {
 // row transform lies inside one wavefront the items need no work-group
 // barrier; rows longer than a wavefront's share synchronise the work-group.
 // ---------------------------------------------------------------------------
+// The largest value over the 64 lanes of a wavefront (no lane holds a NaN).
+__device__ __forceinline__ float wave_max(float x) {
+  auto step = [](float v, auto ctrl) {
+    const int b = __builtin_bit_cast(int, v);
+    return __builtin_fmaxf(
+        v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(b, b, decltype(ctrl)::value, 0xf, 0xf, false)));
+  };
+  x = step(x, std::integral_constant<int, 0x111>{});   // row_shr 1, 2, 4, 8
+  x = step(x, std::integral_constant<int, 0x112>{});
+  x = step(x, std::integral_constant<int, 0x114>{});
+  x = step(x, std::integral_constant<int, 0x118>{});
+  x = step(x, std::integral_constant<int, 0x142>{});   // row_bcast 15, 31: lane 63 holds the maximum
+  x = step(x, std::integral_constant<int, 0x143>{});
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));
+}
+__device__ __forceinline__ double wave_max(double x) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const double o = __shfl_xor(x, off, 64);
+    x = o > x ? o : x;
+  }
+  return x;
+}
+
+// The largest Gamma^2 in range of one wavefront's rows and its smallest
+// sample, written to *out_g / *out_j by one lane.  Over the whole series it
+// takes the maximum of the values alone first; the lane that holds it then
+// looks for its sample.  A restricted range, several lanes with the same value
+// or none with any take the general reduction of (value, sample) pairs.  (That
+// reduction for every row cost 82 instructions of pass 2's 642; this one 37.)
 template <typename Real, class PL>
-__device__ __forceinline__ void pass2_item(cplx<Real> (&v)[2][PL::E2], const PassArgs& a, int item,
-                                           cplx<Real>* buf0, cplx<Real>* buf1, const cplx<Real>* tw, int r, int p,
-                                           int lane, int wave) {
-  constexpr int NW = PL::T2 / 64;
-  const int slot = item / PL::TILES2;
-  const int tile = item - slot * PL::TILES2;
-  const int e = list_entry(a, a.chunk_begin + slot);
-  // row transforms held by one wavefront exchange through LDS without a
-  // work-group barrier
-  constexpr bool WAVE = (64 % PL::P2) == 0;
-  if constexpr (!PL::THREE) pass2_twiddle<Real, PL>(v, tile, r, p);
-  run_stages<Real, PL, PL::N2, PL::E2, typename PL::Rad2, 0, 1, false, WAVE, kPad2>(v, buf0, buf1, tw, p);
-  const SegDesc sg = segment_of(a, e);
+__device__ __forceinline__ void pass2_rows_best(const Real (&gs)[PL::E2], int tile, int64_t j_lo, int64_t j_hi,
+                                                int r, int p, int lane, Real* out_g, int* out_j) {
+  if (j_lo <= 0 && j_hi >= PL::N) {
+    Real m = (Real)-1;   // a NaN is never the larger of two
+#pragma unroll
+    for (int q = 0; q < PL::E2; ++q)
+      m = sizeof(Real) == 4 ? (Real)__builtin_fmaxf((float)m, (float)gs[q]) : gs[q] > m ? gs[q] : m;
+    const Real top = wave_max(m);
+    const unsigned long long tie = __ballot(m == top);
+    if (top >= (Real)0 && (tie & (tie - 1)) == 0) {
+      if (m == top) {
+        int q = PL::E2 - 1;
+#pragma unroll
+        for (int k = PL::E2 - 2; k >= 0; --k) q = gs[k] == m ? k : q;
+        *out_g = m;
+        *out_j = row_base<PL>(tile * PL::RW + r) + PL::ROWS2 * (p + q * PL::P2);
+      }
+      return;
+    }
+  }
   Real g;
   int j;
-  pass2_best<Real, PL>(v, tile, r, p, g, j, sg.j_lo, sg.j_hi);
+  pass2_best_of<Real, PL>(gs, tile, r, p, g, j, j_lo, j_hi);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     const Real go = __shfl_xor(g, off, 64);
@@ -387,56 +443,70 @@ __device__ __forceinline__ void pass2_item(cplx<Real> (&v)[2][PL::E2], const Pas
     }
   }
   if (lane == 0) {
-    const int64_t o = (int64_t)e * a.part_stride + tile * NW + wave;
+    *out_g = g;
+    *out_j = j;
+  }
+}
+
+// One wavefront's best rows, exchanged within the work-group (two sets, used
+// in turn: a set is rewritten only after the next item's barrier).
+template <typename Real, class PL>
+struct RowsBest {
+  Real g[2][PL::T2 / 64];
+  int j[2][PL::T2 / 64];
+};
+
+// The partial of a work item: the best of its wavefronts.
+template <typename Real, class PL>
+__device__ __forceinline__ void pass2_join(const Real (&gs)[PL::E2], const PassArgs& a, int e, int tile,
+                                           int64_t j_lo, int64_t j_hi, int r, int p, RowsBest<Real, PL>& red, int turn) {
+  constexpr int NW = PL::T2 / 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  pass2_rows_best<Real, PL>(gs, tile, j_lo, j_hi, r, p, lane, &red.g[turn][wave], &red.j[turn][wave]);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    Real g = red.g[turn][0];
+    int j = red.j[turn][0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w)
+      if (better(red.g[turn][w], red.j[turn][w], g, j)) {
+        g = red.g[turn][w];
+        j = red.j[turn][w];
+      }
+    const int64_t o = (int64_t)e * a.part_stride + tile;
     ((Real*)a.part_g)[o] = g;
     a.part_j[o] = j;
   }
 }
 
+// Pass 2 on the share of work-group `block` of `nblocks`.
 template <typename Real, class PL>
-__device__ __forceinline__ void pass2_fetch_item(cplx<Real> (&v)[2][PL::E2], const PassArgs& a, int item, int r,
-                                                 int p) {
-  const int slot = item / PL::TILES2;
-  pass2_fetch<Real, PL>(v, (const cplx<Real>*)a.ws + (int64_t)slot * 2 * PL::N, item - slot * PL::TILES2, r, p);
-}
-
-// Pass 2 on the items of `a` taken by work-group `block` of `nblocks` (tw holds
-// the length-N2 twiddles).
-template <typename Real, class PL>
-__device__ __forceinline__ void pass2_body(const PassArgs& a, cplx<Real>* lds, const cplx<Real>* tw, int block,
+__device__ __forceinline__ void pass2_body(const PassArgs& a, cplx<Real>* lds, RowsBest<Real, PL>& red, int block,
                                            int nblocks) {
   constexpr int LP = PassLds<Real, PL>::LP2;
   const int tid = threadIdx.x;
-  const int items = launch_span(a) * PL::TILES2;
+  const int span = launch_span(a);
+  int tile, slot, step;
+  tile_of_block<PL::TILES2>(block, nblocks, tile, slot, step);
+  if (slot >= span) return;
   const int p = tid % PL::P2, r = tid / PL::P2;
   cplx<Real>* buf0 = lds + r * LP;
-  cplx<Real>* buf1 = kJointExchange<Real> ? lds + (PL::RW + r) * LP : buf0;
-  const int lane = tid & 63, wave = tid >> 6;
-  // software pipeline over two register sets: the rows of the next item are
-  // fetched while this one is transformed
-  // (the fetches are unconditional, a missing next item replaced by one
-  // already fetched, so that every path has the same loads in flight and the
-  // compiler's wait counts only wait for the set being transformed)
-  if constexpr (!PassTune<Real, PL>::prefetch2) {
-    // one register set: each item's rows are loaded when it starts
-    for (int item = block; item < items; item += nblocks) {
-      cplx<Real> v[2][PL::E2];
-      pass2_fetch_item<Real, PL>(v, a, item, r, p);
-      pass2_item<Real, PL>(v, a, item, buf0, buf1, tw, r, p, lane, wave);
-    }
-    return;
-  }
-  cplx<Real> va[2][PL::E2], vb[2][PL::E2];
-  int item = block;
-  if (item < items) pass2_fetch_item<Real, PL>(va, a, item, r, p);
-  while (item < items) {
-    const int next = item + nblocks;
-    pass2_fetch_item<Real, PL>(vb, a, next < items ? next : item, r, p);
-    pass2_item<Real, PL>(va, a, item, buf0, buf1, tw, r, p, lane, wave);
-    if (next >= items) break;
-    item = next + nblocks;
-    pass2_fetch_item<Real, PL>(va, a, item < items ? item : next, r, p);
-    pass2_item<Real, PL>(vb, a, next, buf0, buf1, tw, r, p, lane, wave);
+  cplx<Real>* buf1 = PassTune<Real, PL>::joint2 ? lds + (PL::RW + r) * LP : buf0;
+  int turn = 0;
+  Pass2Geo<Real, PL> geo;
+  geo.init(p, tile * PL::RW + r, PL::THREE ? 1 : PL::N1);
+  for (; slot < span; slot += step) {
+    const int e = list_entry(a, a.chunk_begin + slot);
+    cplx<Real> v[2][PL::E2];
+    pass2_fetch<Real, PL>(v, (const cplx<Real>*)a.ws + (int64_t)slot * 2 * PL::N, tile, r, p);
+    const SegDesc sg = segment_of(a, e);
+    const int64_t j_lo = sg.j_lo, j_hi = sg.j_hi;
+    // row transforms held by one wavefront exchange through LDS without a
+    // work-group barrier
+    Real g[PL::E2];
+    pass2_transform<Real, PL, kRowInWave<PL>>(v, g, buf0, buf1, geo, p);
+    pass2_join<Real, PL>(g, a, e, tile, j_lo, j_hi, r, p, red, turn);
+    turn ^= 1;
   }
 }
 
@@ -444,131 +514,78 @@ template <typename Real, class PL>
 __global__ void __launch_bounds__(PL::T2)
     __attribute__((amdgpu_waves_per_eu(PassTune<Real, PL>::waves2))) k_pass2(PassArgs a) {
   __shared__ cplx<Real> lds[PassLds<Real, PL>::X2];
-  __shared__ cplx<Real> tw[PL::N2];
-  init_twiddles<Real, PL::N2, PL::T2>(tw);
-  pass2_body<Real, PL>(a, lds, tw, blockIdx.x, gridDim.x);
+  __shared__ RowsBest<Real, PL> red;
+  pass2_body<Real, PL>(a, lds, red, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
-// Finalize: one wavefront per point reduces its pass-2 partials.
+// Finalize: Gamma^2 and j* of a point from its pass-2 partials; -inf / -1
+// outside the rectangle, NaN / -2 for a bad segment.  By a group of G lanes
+// (aligned, every lane of the group calling it): the largest value, then
+// smallest sample, is unique, so any grouping of the reduction gives the same
+// result.
 // ---------------------------------------------------------------------------
-// Gamma^2 and j* of point e from its partials, by the 64 lanes of one
-// wavefront (lane 0 writes them); -inf / -1 outside the rectangle, NaN / -2
-// for a bad segment.
-template <typename Real>
-__device__ __forceinline__ void finalize_point(const EvalDesc& ev, const Real* __restrict__ part_g,
-                                               const int32_t* __restrict__ part_j, int part_stride,
-                                               const int32_t* __restrict__ plan_parts2, int e, int lane,
-                                               double* __restrict__ fitness, int32_t* __restrict__ argmax) {
-  const int status = ev.status;
-  if (status != 1) {
-    if (lane == 0) {
-      fitness[e] = status == 0 ? -INFINITY : NAN;
-      argmax[e] = status == 0 ? -1 : -2;
-    }
-    return;
-  }
-  const int nt = plan_parts2[ev.plan];
-  Real g = (Real)-1;
-  int j = 0x7fffffff;
-  for (int t = lane; t < nt; t += 64) {
-    const Real go = part_g[(int64_t)e * part_stride + t];
-    const int jo = part_j[(int64_t)e * part_stride + t];
-    if (better(go, jo, g, j)) {
-      g = go;
-      j = jo;
-    }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const Real go = __shfl_xor(g, off, 64);
-    const int jo = __shfl_xor(j, off, 64);
-    if (better(go, jo, g, j)) {
-      g = go;
-      j = jo;
-    }
-  }
-  if (lane == 0) {
-    fitness[e] = (double)g;
-    argmax[e] = j;
-  }
-}
-
-// The same by a group of 8 lanes (lane g of the group, groups aligned to 8
-// lanes, every lane of the group calling it): the largest (g, then smallest j)
-// of the partials is unique, so any grouping of the reduction gives the same
-// result as finalize_point.
-template <typename Real>
+template <typename Real, int G>
 __device__ __forceinline__ void finalize_group(const EvalDesc& ev, const Real* __restrict__ part_g,
                                                const int32_t* __restrict__ part_j, int part_stride,
                                                const int32_t* __restrict__ plan_parts2, int e, int g,
                                                double* __restrict__ fitness, int32_t* __restrict__ argmax) {
   const int status = ev.status;
-  if (status != 1) {
-    if (g == 0) {
-      fitness[e] = status == 0 ? -INFINITY : NAN;
-      argmax[e] = status == 0 ? -1 : -2;
-    }
-    return;
-  }
-  const int nt = plan_parts2[ev.plan];
   Real bg = (Real)-1;
   int bj = 0x7fffffff;
-  // batches of 16 loads per lane in flight before any is compared
-  constexpr int B = 16;
-  for (int t0 = g; t0 < nt; t0 += 8 * B) {
-    Real gv[B];
-    int jv[B];
+  if (status == 1) {
+    const int nt = plan_parts2[ev.plan];
+    // batches of B loads per lane in flight before any is compared
+    constexpr int B = G >= 64 ? 8 : 16;
+    for (int t0 = g; t0 < nt; t0 += G * B) {
+      Real gv[B];
+      int jv[B];
 #pragma unroll
-    for (int u = 0; u < B; ++u) {
-      const int t = t0 + 8 * u;
-      gv[u] = t < nt ? part_g[(int64_t)e * part_stride + t] : (Real)-1;
-      jv[u] = t < nt ? part_j[(int64_t)e * part_stride + t] : 0x7fffffff;
+      for (int u = 0; u < B; ++u) {
+        const int t = t0 + G * u;
+        gv[u] = t < nt ? part_g[(int64_t)e * part_stride + t] : (Real)-1;
+        jv[u] = t < nt ? part_j[(int64_t)e * part_stride + t] : 0x7fffffff;
+      }
+#pragma unroll
+      for (int u = 0; u < B; ++u)
+        if (better(gv[u], jv[u], bg, bj)) {
+          bg = gv[u];
+          bj = jv[u];
+        }
     }
 #pragma unroll
-    for (int u = 0; u < B; ++u)
-      if (better(gv[u], jv[u], bg, bj)) {
-        bg = gv[u];
-        bj = jv[u];
+    for (int off = G / 2; off > 0; off >>= 1) {
+      const Real go = __shfl_xor(bg, off, G);
+      const int jo = __shfl_xor(bj, off, G);
+      if (better(go, jo, bg, bj)) {
+        bg = go;
+        bj = jo;
       }
-  }
-#pragma unroll
-  for (int off = 4; off > 0; off >>= 1) {
-    const Real go = __shfl_xor(bg, off, 8);
-    const int jo = __shfl_xor(bj, off, 8);
-    if (better(go, jo, bg, bj)) {
-      bg = go;
-      bj = jo;
     }
   }
   if (g == 0) {
-    fitness[e] = (double)bg;
-    argmax[e] = bj;
+    fitness[e] = status == 1 ? (double)bg : status == 0 ? -INFINITY : NAN;
+    argmax[e] = status == 1 ? bj : status == 0 ? -1 : -2;
   }
 }
 
 template <typename Real>
-__global__ void __launch_bounds__(256) k_finalize(const EvalDesc* __restrict__ evals,
-                                                  const SegDesc* __restrict__ segs, const Real* __restrict__ part_g,
+__global__ void __launch_bounds__(256) k_finalize(const EvalDesc* __restrict__ evals, const Real* __restrict__ part_g,
                                                   const int32_t* __restrict__ part_j, int n, int part_stride,
                                                   const int32_t* __restrict__ plan_parts2,
                                                   int32_t* __restrict__ counts,
                                                   unsigned long long* __restrict__ evaluated,
                                                   double* __restrict__ fitness, int32_t* __restrict__ argmax) {
-  const int lane = threadIdx.x & 63;
   const int e = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (blockIdx.x == 0 && threadIdx.x < kNumPlans) {
     // running total of points evaluated (inside the rectangle); the passes of
     // this call are done with the list counts, which start the next call at 0
-    unsigned long long t = 0;
-    for (int p = 0; p < kNumPlans; ++p) {
-      t += (unsigned long long)counts[p];
-      counts[p] = 0;
-    }
-    atomicAdd(evaluated, t);
+    const int c = counts[threadIdx.x];
+    counts[threadIdx.x] = 0;
+    if (c) atomicAdd(evaluated, (unsigned long long)c);
   }
   if (e >= n) return;
-  finalize_point<Real>(evals[e], part_g, part_j, part_stride, plan_parts2, e, lane, fitness, argmax);
+  finalize_group<Real, 64>(evals[e], part_g, part_j, part_stride, plan_parts2, e, threadIdx.x & 63, fitness, argmax);
 }
 
 }  // namespace fcas
@@ -625,20 +642,14 @@ __global__ void __launch_bounds__(PL::T1) k_fused(FusedArgs f) {
   static_assert(!PL::THREE, "the fused schedule covers two-pass plans");
   constexpr int LP1 = lds_padded_len<kPad1>(PL::N1), LP2 = lds_padded_len<kPad2>(PL::N2);
   constexpr int LDSN = 2 * ((PL::C * LP1 > PL::RW * LP2) ? PL::C * LP1 : PL::RW * LP2);
-  constexpr int NW = PL::T2 / 64;
   constexpr int T1 = PL::TILES1, T2 = PL::TILES2, T = T1 + T2;
   __shared__ cplx<Real> lds[LDSN];
-  __shared__ cplx<Real> tw1[PL::N1];
-  __shared__ cplx<Real> tw2[PL::N2];
+  __shared__ RowsBest<Real, PL> red;
   const PassArgs& a = f.p;
   const int tid = threadIdx.x;
-  for (int m = tid; m < PL::N1; m += PL::T1) tw1[m] = twiddle<Real>(m, PL::N1);
-  for (int m = tid; m < PL::N2; m += PL::T1) tw2[m] = twiddle<Real>(m, PL::N2);
-  __syncthreads();
   const int cnt = *a.count;
   const int L = f.lag < cnt ? f.lag : cnt;
   const int total = cnt * T;
-  const int lane = tid & 63, wave = tid >> 6;
   for (int item = blockIdx.x; item < total; item += gridDim.x) {
     int kind, ep, tile;
     fused_decode(item, cnt, L, T1, T2, kind, ep, tile);
@@ -651,33 +662,22 @@ __global__ void __launch_bounds__(PL::T1) k_fused(FusedArgs f) {
       const SegDesc& sg = a.segs[ev.seg];
       const int c = tid % PL::C, p = tid / PL::C;
       cplx<Real> v[2][PL::E1];
+      Pass1Geo<Real, PL> geo;
+      geo.init(p);
       pass1_prologue<Real, PL>(v, ev, sg, a.n_det, tile, c, p);
-      run_stages<Real, PL, PL::N1, PL::E1, typename PL::Rad1, 0, 1, true, false, kPad1>(v, lds + c * LP1, lds + (PL::C + c) * LP1,
-                                                                          tw1, p);
-      pass1_store<Real, PL>(v, ws, tile, c, p);
+      pass1_transform<Real, PL, false>(v, ws, lds + c * LP1, lds + (PL::C + c) * LP1, geo, tile, c, p);
       signal_count(f.done1 + ep);
     } else {
       wait_count(f.done1 + ep, T1, f.max_spin, f.err);
       const int p = tid % PL::P2, r = tid / PL::P2;
       cplx<Real> v[2][PL::E2];
-      pass2_load<Real, PL>(v, ws, tile, r, p);
-      run_stages<Real, PL, PL::N2, PL::E2, typename PL::Rad2, 0, 1, false, false, kPad2>(v, lds + r * LP2, lds + (PL::RW + r) * LP2, tw2,
-                                                                   p);
-      const SegDesc& sg = a.segs[a.evals[e].seg];
-      Real g;
-      int j;
-      pass2_best<Real, PL>(v, tile, r, p, g, j, sg.j_lo, sg.j_hi);
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        const Real go = __shfl_xor(g, off, 64);
-        const int jo = __shfl_xor(j, off, 64);
-        if (better(go, jo, g, j)) { g = go; j = jo; }
-      }
-      if (lane == 0) {
-        const int64_t o = (int64_t)e * a.part_stride + tile * NW + wave;
-        ((Real*)a.part_g)[o] = g;
-        a.part_j[o] = j;
-      }
+      pass2_fetch<Real, PL>(v, ws, tile, r, p);
+      Pass2Geo<Real, PL> geo;
+      geo.init(p, tile * PL::RW + r, PL::N1);
+      Real g[PL::E2];
+      pass2_transform<Real, PL, false>(v, g, lds + r * LP2, lds + (PL::RW + r) * LP2, geo, p);
+      const SegDesc sg = segment_of(a, e);
+      pass2_join<Real, PL>(g, a, e, tile, sg.j_lo, sg.j_hi, r, p, red, 0);
       signal_count(f.done2 + ep);
     }
   }

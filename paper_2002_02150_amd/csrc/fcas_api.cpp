@@ -20,7 +20,19 @@ using namespace fcas;
 
 namespace {
 
-constexpr int kDefaultGrid = 2048;   // persistent work-groups of a pass launch unless tuned
+// Work-groups of a pass launch unless tuned.  Pass 1 keeps a tile's segment
+// data from point to point and wants few (two rounds of what is resident);
+// pass 2 reads its rows afresh and is fastest with one or two points each: 320
+// points of 131072 take it 126 us with 1024 work-groups, 106 with 16384 (pass 1
+// 118 with 1024, 150 with 8192).
+constexpr int kDefaultGrid1 = 1024, kDefaultGrid2 = 16384;
+
+// Pass-1 output of a launch beyond which its stores are non-temporal.
+// Measured: 192 points of 131072 (403 MB) 87 us with non-temporal stores, 86
+// through the L2; 2048 points (4.3 GB) 800 and 835; shorter lengths of smaller
+// launches gain more from the L2 (320 points of 65536: 75 and 61; 196608: 202
+// and 183).
+constexpr size_t kNtBytes = (size_t)1 << 30;
 
 thread_local std::string g_last_error;
 
@@ -234,8 +246,8 @@ int fcas_select_plan(fcas_ctx* ctx, int32_t plan, int32_t grid1, int32_t grid2) 
   if (grid1 < 0 || grid2 < 0 || grid1 > (1 << 20) || grid2 > (1 << 20))
     return fail(FCAS_EINVAL, "grid sizes must be in [0, 2^20]");
   ctx->chosen[plan_for_length(kPlans[plan].n)] = plan;
-  ctx->grid1[plan] = grid1 > 0 ? grid1 : kDefaultGrid;
-  ctx->grid2[plan] = grid2 > 0 ? grid2 : kDefaultGrid;
+  ctx->grid1[plan] = grid1 > 0 ? grid1 : kDefaultGrid1;
+  ctx->grid2[plan] = grid2 > 0 ? grid2 : kDefaultGrid2;
   return FCAS_OK;
 }
 
@@ -265,7 +277,8 @@ int fcas_create(const fcas_network* net, const fcas_config* cfg, int device, fca
   c->cfg = *cfg;
   c->prec = cfg->precision == FCAS_FP64 ? 1 : 0;
   for (int i = 0; i < kNumPlans; ++i) {
-    c->grid1[i] = c->grid2[i] = kDefaultGrid;
+    c->grid1[i] = kDefaultGrid1;
+    c->grid2[i] = kDefaultGrid2;
     c->chosen[i] = i;
   }
   c->schedule = c->prec == 0 ? cfg->schedule : FCAS_SCHEDULE_TWO_PASS;
@@ -501,6 +514,10 @@ struct EvalBufs {
   int list_stride;
 };
 
+// Grid of a tiled pass over m points: whole groups of one work-group per tile,
+// as many as the chosen grid holds (at least one, at most one per point).
+int tile_grid(int tiles, int m, int grid) { return tiles * std::max(1, std::min(grid / tiles, m)); }
+
 EvalBufs own_bufs(const fcas_ctx* ctx) {
   return EvalBufs{ctx->d_evals, ctx->d_lists, ctx->d_counts, ctx->d_part_g, ctx->d_part_j,
                   ctx->d_ws, ctx->ws_bytes, ctx->cfg.max_batch};
@@ -531,6 +548,7 @@ PassArgs pass_args(fcas_ctx* ctx, const EvalBufs& b, int plan, int cap) {
   a.n_det = ctx->net.n_det;
   a.chunk_begin = 0;
   a.cap = cap;
+  a.nt = 0;
   return a;
 }
 
@@ -625,8 +643,9 @@ int enqueue_passes(fcas_ctx* ctx, const EvalBufs& b, int32_t n, double* d_fitnes
     for (int begin = 0; begin < n; begin += cap) {
       a.chunk_begin = begin;
       const int m = std::min(cap, n - begin);
-      const int g1 = std::min(m * pi.tiles1[ctx->prec], ctx->grid1[plan]);
-      const int g2 = std::min(m * pi.tiles2[ctx->prec], ctx->grid2[plan]);
+      a.nt = m * slot_bytes > kNtBytes ? 1 : 0;
+      const int g1 = tile_grid(pi.tiles1[ctx->prec], m, ctx->grid1[plan]);
+      const int g2 = tile_grid(pi.tiles2[ctx->prec], m, ctx->grid2[plan]);
       const char* what = nullptr;
       if ((e = timed_launch(ctx, ctx->t_pass1, s, 1, plan, a, g1)) != hipSuccess) what = "pass-1 launch";
       if (!what && pi.nm > 1) {
@@ -642,7 +661,7 @@ int enqueue_passes(fcas_ctx* ctx, const EvalBufs& b, int32_t n, double* d_fitnes
   }
   ctx->timing = was_timing;
   if (!finalize) return FCAS_OK;
-  if ((e = launch_finalize(ctx->prec, b.evals, ctx->d_segs, b.part_g, b.part_j, n, ctx->part_stride,
+  if ((e = launch_finalize(ctx->prec, b.evals, b.part_g, b.part_j, n, ctx->part_stride,
                            ctx->d_plan_parts2, b.counts, ctx->d_evaluated, d_fitness, d_argmax, s)) != hipSuccess)
     return hip_fail(e, "finalize launch");
   return FCAS_OK;
@@ -831,20 +850,33 @@ int fcas_read_timing(fcas_ctx* ctx, const char* which, double* total_ms, int64_t
 
 // precision dispatch of the pass launchers (the instantiations live in eval_f32.hip / eval_f64.hip)
 namespace fcas {
-hipError_t launch_pass1_f32(int plan, const PassArgs& a, int grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
-hipError_t launch_pass1_f64(int plan, const PassArgs& a, int grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
+#define FCAS_EACH_DT(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
+#define FCAS_DECLARE_DT(DT)                                                                                        \
+  template <>                                                                                                      \
+  hipError_t launch_pass1_dt<float, DT>(int, const PassArgs&, int, hipStream_t, hipEvent_t, hipEvent_t);           \
+  template <>                                                                                                      \
+  hipError_t launch_pass1_dt<double, DT>(int, const PassArgs&, int, hipStream_t, hipEvent_t, hipEvent_t);
+FCAS_EACH_DT(FCAS_DECLARE_DT)
 hipError_t launch_passm_f32(int plan, const PassArgs& a, int grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_passm_f64(int plan, const PassArgs& a, int grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_pass2_f32(int plan, const PassArgs& a, int grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_pass2_f64(int plan, const PassArgs& a, int grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
-hipError_t launch_finalize_f32(const EvalDesc*, const SegDesc*, const void*, const int32_t*, int, int, const int32_t*,
-                               int32_t*, unsigned long long*, double*, int32_t*, hipStream_t);
-hipError_t launch_finalize_f64(const EvalDesc*, const SegDesc*, const void*, const int32_t*, int, int, const int32_t*,
-                               int32_t*, unsigned long long*, double*, int32_t*, hipStream_t);
+hipError_t launch_finalize_f32(const EvalDesc*, const void*, const int32_t*, int, int, const int32_t*, int32_t*,
+                               unsigned long long*, double*, int32_t*, hipStream_t);
+hipError_t launch_finalize_f64(const EvalDesc*, const void*, const int32_t*, int, int, const int32_t*, int32_t*,
+                               unsigned long long*, double*, int32_t*, hipStream_t);
 
 hipError_t launch_pass1(int precision, int plan, const PassArgs& a, int grid, hipStream_t s, hipEvent_t e0,
                         hipEvent_t e1) {
-  return precision ? launch_pass1_f64(plan, a, grid, s, e0, e1) : launch_pass1_f32(plan, a, grid, s, e0, e1);
+#define FCAS_CASE_DT(DT)                                                       \
+  case DT:                                                                     \
+    return precision ? launch_pass1_dt<double, DT>(plan, a, grid, s, e0, e1)   \
+                     : launch_pass1_dt<float, DT>(plan, a, grid, s, e0, e1);
+  switch (a.n_det) {
+    FCAS_EACH_DT(FCAS_CASE_DT)
+    default:
+      return hipErrorInvalidValue;
+  }
 }
 hipError_t launch_passm(int precision, int plan, const PassArgs& a, int grid, hipStream_t s, hipEvent_t e0,
                         hipEvent_t e1) {
@@ -854,14 +886,11 @@ hipError_t launch_pass2(int precision, int plan, const PassArgs& a, int grid, hi
                         hipEvent_t e1) {
   return precision ? launch_pass2_f64(plan, a, grid, s, e0, e1) : launch_pass2_f32(plan, a, grid, s, e0, e1);
 }
-hipError_t launch_finalize(int precision, const EvalDesc* evals, const SegDesc* segs, const void* part_g,
-                           const int32_t* part_j, int n, int part_stride, const int32_t* plan_parts2,
-                           int32_t* counts, unsigned long long* evaluated, double* fitness, int32_t* argmax,
-                           hipStream_t s) {
-  return precision ? launch_finalize_f64(evals, segs, part_g, part_j, n, part_stride, plan_parts2, counts, evaluated,
-                                         fitness, argmax, s)
-                   : launch_finalize_f32(evals, segs, part_g, part_j, n, part_stride, plan_parts2, counts, evaluated,
-                                         fitness, argmax, s);
+hipError_t launch_finalize(int precision, const EvalDesc* evals, const void* part_g, const int32_t* part_j, int n,
+                           int part_stride, const int32_t* plan_parts2, int32_t* counts,
+                           unsigned long long* evaluated, double* fitness, int32_t* argmax, hipStream_t s) {
+  return (precision ? launch_finalize_f64 : launch_finalize_f32)(evals, part_g, part_j, n, part_stride, plan_parts2,
+                                                                 counts, evaluated, fitness, argmax, s);
 }
 }  // namespace fcas
 

@@ -143,12 +143,13 @@ FCAS_HD void stream_store(cplx<R>* p, cplx<R> v) {
 #endif
 }
 
-// Non-temporal stores into one region of the workspace through a buffer
-// resource (base and size in scalar registers).  A store's byte offset is a
-// per-thread part (a vector register) plus a uniform part (a scalar register
-// or constant), so the stores of a thread at compile-time strides share one
-// address computation instead of a 64-bit address each.  The region is at
-// most 2^32 - 1 bytes; the hardware drops a store past its end.
+// Stores into one region of the workspace through a buffer resource (base and
+// size in scalar registers).  A store's byte offset is a per-thread part (a
+// vector register) plus a uniform part (a scalar register or constant), so the
+// stores of a thread at compile-time strides share one address computation
+// instead of a 64-bit address each.  The region is at most 2^32 - 1 bytes; the
+// hardware drops a store past its end.
+// NT: non-temporal, else written through the L2 (device scope).
 template <typename R>
 struct StreamOut {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -156,13 +157,15 @@ struct StreamOut {
   FCAS_HD StreamOut(cplx<R>* base, int64_t elems)
       : rs(__builtin_amdgcn_make_buffer_rsrc(base, 0, (int)(elems * (int64_t)sizeof(cplx<R>)), kRsrcWord3)) {}
   // element `vo + so` of the region, vo per thread, so uniform
+  template <bool NT>
   FCAS_HD void store(int vo, int so, cplx<R> v) const {
+    constexpr int kPolicy = NT ? 2 : 16;   // cache policy bits: nt, sc1
     if constexpr (sizeof(R) == 4) {
       typedef int i2 __attribute__((ext_vector_type(2)));
       i2 t;
       t.x = __builtin_bit_cast(int, v.x);
       t.y = __builtin_bit_cast(int, v.y);
-      __builtin_amdgcn_raw_buffer_store_b64(t, rs, vo * (int)sizeof(cplx<R>), so * (int)sizeof(cplx<R>), kNt);
+      __builtin_amdgcn_raw_buffer_store_b64(t, rs, vo * (int)sizeof(cplx<R>), so * (int)sizeof(cplx<R>), kPolicy);
     } else {
       typedef int i4 __attribute__((ext_vector_type(4)));
       const long long xr = __builtin_bit_cast(long long, v.x), yr = __builtin_bit_cast(long long, v.y);
@@ -171,16 +174,15 @@ struct StreamOut {
       t.y = (int)(xr >> 32);
       t.z = (int)yr;
       t.w = (int)(yr >> 32);
-      __builtin_amdgcn_raw_buffer_store_b128(t, rs, vo * (int)sizeof(cplx<R>), so * (int)sizeof(cplx<R>), kNt);
+      __builtin_amdgcn_raw_buffer_store_b128(t, rs, vo * (int)sizeof(cplx<R>), so * (int)sizeof(cplx<R>), kPolicy);
     }
   }
-  // descriptor word 3 of an untyped gfx9 buffer (32-bit data format); cache
-  // policy of the stores: non-temporal
+  // descriptor word 3 of an untyped gfx9 buffer (32-bit data format)
   static constexpr int kRsrcWord3 = 0x00020000;
-  static constexpr int kNt = 2;
 #else
   cplx<R>* base;
   FCAS_HD StreamOut(cplx<R>* b, int64_t) : base(b) {}
+  template <bool NT>
   FCAS_HD void store(int vo, int so, cplx<R> v) const { base[(int64_t)vo + so] = v; }
 #endif
 };
@@ -258,6 +260,51 @@ FCAS_HD void dft15(cplx<T>* x) {
   }
 }
 
+// 12 = 3 x 4 by the same algorithm: input n = (4 n1 + 3 n2) mod 12, output
+// k = (4 k1 + 9 k2) mod 12 (4 = 1 mod 3, 9 = 1 mod 4); four 3-point transforms
+// over n1, then three 4-point transforms over n2.  HALF: x[6..12) are zero and
+// need not be initialised.
+template <bool HALF, typename T>
+FCAS_HD void dft12(cplx<T>* x) {
+  const T h = (T)0.86602540378443864676, r = (T)0.5;
+  cplx<T> y[4][3];
+  if constexpr (HALF) {
+    {   // x0, x4, 0
+      const cplx<T> a = x[0], b = x[4];
+      const cplx<T> m = mk<T>(a.x - r * b.x, a.y - r * b.y);
+      y[0][0] = add(a, b);
+      y[0][1] = mk<T>(m.x - h * b.y, m.y + h * b.x);
+      y[0][2] = mk<T>(m.x + h * b.y, m.y - h * b.x);
+    }
+    y[1][0] = y[1][1] = y[1][2] = x[3];   // x3, 0, 0
+    {   // 0, 0, x2
+      const cplx<T> c = x[2], m = mk<T>(-r * c.x, -r * c.y);
+      y[2][0] = c;
+      y[2][1] = mk<T>(m.x + h * c.y, m.y - h * c.x);
+      y[2][2] = mk<T>(m.x - h * c.y, m.y + h * c.x);
+    }
+    {   // 0, x1, x5
+      const cplx<T> s = add(x[1], x[5]), d = sub(x[1], x[5]), m = mk<T>(-r * s.x, -r * s.y);
+      y[3][0] = s;
+      y[3][1] = mk<T>(m.x - h * d.y, m.y + h * d.x);
+      y[3][2] = mk<T>(m.x + h * d.y, m.y - h * d.x);
+    }
+  } else {
+#pragma unroll
+    for (int n2 = 0; n2 < 4; ++n2) {
+      y[n2][0] = x[(3 * n2) % 12]; y[n2][1] = x[(4 + 3 * n2) % 12]; y[n2][2] = x[(8 + 3 * n2) % 12];
+      dft3(y[n2][0], y[n2][1], y[n2][2]);
+    }
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < 3; ++k1) {
+    cplx<T> z[4] = {y[0][k1], y[1][k1], y[2][k1], y[3][k1]};
+    dft4(z[0], z[1], z[2], z[3]);
+#pragma unroll
+    for (int k2 = 0; k2 < 4; ++k2) x[(4 * k1 + 9 * k2) % 12] = z[k2];
+  }
+}
+
 // Last step of an 8-point DFT from the 4-point DFTs of the even (e) and odd
 // (o) inputs: X[j] = e_j + w8^j o_j, X[j+4] = e_j - w8^j o_j.  The 1/sqrt2 of
 // w8^1 = (1+i)/sqrt2 and w8^3 = (-1+i)/sqrt2 is applied inside the sums, each
@@ -330,6 +377,8 @@ FCAS_HD void dft_half(cplx<T>* x) {
     x[1] = x[0];
   } else if constexpr (R == 4) {
     dft4_half(x[0], x[1], x[2], x[3]);
+  } else if constexpr (R == 12) {
+    dft12<true>(x);
   } else if constexpr (R == 8) {
     cplx<T> e0 = x[0], e1 = x[2], e2, e3, o0 = x[1], o1 = x[3], o2, o3;
     dft4_half(e0, e1, e2, e3);
@@ -357,7 +406,7 @@ FCAS_HD void dft_half(cplx<T>* x) {
       x[c] = b0; x[c + 4] = b1; x[c + 8] = b2; x[c + 12] = b3;
     }
   } else {
-    static_assert(R == 2 || R == 4 || R == 8 || R == 16, "unsupported half-input radix");
+    static_assert(R == 2 || R == 4 || R == 8 || R == 12 || R == 16, "unsupported half-input radix");
   }
 }
 
@@ -371,6 +420,8 @@ FCAS_HD void dft(cplx<T>* x) {
     dft4(x[0], x[1], x[2], x[3]);
   } else if constexpr (R == 5) {
     dft5(x);
+  } else if constexpr (R == 12) {
+    dft12<false>(x);
   } else if constexpr (R == 8) {
     dft8(x);
   } else if constexpr (R == 15) {
@@ -378,7 +429,143 @@ FCAS_HD void dft(cplx<T>* x) {
   } else if constexpr (R == 16) {
     dft16(x);
   } else {
-    static_assert(R == 2 || R == 3 || R == 4 || R == 5 || R == 8 || R == 15 || R == 16, "unsupported radix");
+    static_assert(R == 2 || R == 3 || R == 4 || R == 5 || R == 8 || R == 12 || R == 15 || R == 16, "unsupported radix");
+  }
+}
+
+// ---------------------------------------------------------------------------
+// DFTs of inputs whose twiddles are the powers of one ratio s:
+//   X[c] = sum_p x[p] s^p w_R^{pc}.
+// Every later stage of a transform has that form, and so has a transform
+// shifted by a fraction of a sample (the four-step twiddle).  Halving p gives
+// butterflies x[p] +- s^{R/2} x[p + R/2], whose halves are transforms of half
+// the length with the ratios s and s w_R: the twiddles never multiply an
+// input, they only appear as the factor of a butterfly, where a + w b is two
+// fused multiply-adds per component and a - w b = 2 a - (a + w b) one more.  A
+// radix-8 stage takes 72 instructions so, against 80 with seven twiddle
+// products, and four distinct factors against seven.
+// ---------------------------------------------------------------------------
+// (a, b) -> (a + w b, a - w b), the factor i w instead of w if I.
+template <bool I, typename T>
+FCAS_HD void geo2(cplx<T>& a, cplx<T>& b, cplx<T> w) {
+  const T wr = I ? -w.y : w.x, wi = I ? w.x : w.y;
+  const T px = a.x + wr * b.x - wi * b.y, py = a.y + wr * b.y + wi * b.x;
+  b = mk<T>((T)2 * a.x - px, (T)2 * a.y - py);
+  a = mk<T>(px, py);
+}
+
+// t = s^2 (i t if TI), s
+template <bool TI, typename T>
+FCAS_HD void geo4(cplx<T>* x, cplx<T> t, cplx<T> s) {
+  geo2<TI>(x[0], x[2], t);
+  geo2<TI>(x[1], x[3], t);
+  geo2<false>(x[0], x[1], s);
+  geo2<true>(x[2], x[3], s);
+  const cplx<T> x1 = x[2];
+  x[2] = x[1];
+  x[1] = x1;
+}
+
+// u = s^4 (i u if UI), t = s^2, s, r = s w8
+template <bool UI, typename T>
+FCAS_HD void geo8(cplx<T>* x, cplx<T> u, cplx<T> t, cplx<T> s, cplx<T> r) {
+  cplx<T> a[4], b[4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    a[p] = x[p];
+    b[p] = x[p + 4];
+    geo2<UI>(a[p], b[p], u);
+  }
+  geo4<false>(a, t, s);
+  geo4<true>(b, t, r);
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    x[2 * p] = a[p];
+    x[2 * p + 1] = b[p];
+  }
+}
+
+// Distinct factors of a radix-R transform with ratio s: factor f is
+// s^geo_mul(R, f) w_16^geo_off(R, f).
+constexpr int geo_count(int R) { return R == 2 ? 1 : R == 3 || R == 4 ? 2 : R == 8 ? 4 : R == 16 ? 8 : 0; }
+constexpr int geo_mul(int R, int f) {
+  if (R == 3) return f + 1;
+  if (R == 4) return f == 0 ? 2 : 1;
+  if (R == 8) return f == 0 ? 4 : f == 1 ? 2 : 1;
+  if (R == 16) return f == 0 ? 8 : f == 1 ? 4 : f < 4 ? 2 : 1;
+  return 1;
+}
+constexpr int geo_off(int R, int f) {
+  if (R == 8) return f == 3 ? 2 : 0;
+  if (R == 16) return f == 3 ? 2 : f > 4 ? f - 4 : 0;
+  return 0;
+}
+
+template <int R, typename T>
+FCAS_HD void dft_geo(cplx<T>* x, const cplx<T>* w) {
+  if constexpr (R == 2) {
+    geo2<false>(x[0], x[1], w[0]);
+  } else if constexpr (R == 3) {
+    x[1] = mul(x[1], w[0]);
+    x[2] = mul(x[2], w[1]);
+    dft3(x[0], x[1], x[2]);
+  } else if constexpr (R == 4) {
+    geo4<false>(x, w[0], w[1]);
+  } else if constexpr (R == 8) {
+    geo8<false>(x, w[0], w[1], w[2], w[3]);
+  } else if constexpr (R == 16) {
+    cplx<T> a[8], b[8];
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      a[p] = x[p];
+      b[p] = x[p + 8];
+      geo2<false>(a[p], b[p], w[0]);
+    }
+    geo8<false>(a, w[1], w[2], w[4], w[6]);
+    geo8<true>(b, w[1], w[3], w[5], w[7]);   // ratio s w16: its fourth power is i s^4
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      x[2 * p] = a[p];
+      x[2 * p + 1] = b[p];
+    }
+  } else {
+    static_assert(R == 2 || R == 3 || R == 4 || R == 8 || R == 16, "unsupported radix");
+  }
+}
+
+// The factors of ratio s = exp(2 pi i num / den), num / den < 1 / R.  Float:
+// each from its own hardware sine and cosine (powers of s would multiply
+// their error: 4e-7 of the fitness became 1.6e-6); double: powers of s (error
+// of a few 1e-16).
+template <int R, typename T>
+FCAS_HD void geo_factors(cplx<T>* w, int num, int den) {
+  if constexpr (sizeof(T) == 4) {
+#pragma unroll
+    for (int f = 0; f < geo_count(R); ++f) {
+      if (R == 8 && f == 3) {   // s w8
+        const T h = (T)0.70710678118654752440;
+        w[3] = mk<T>(h * (w[2].x - w[2].y), h * (w[2].x + w[2].y));
+        continue;
+      }
+      T r = (T)(geo_mul(R, f) * num) / (T)den + (T)geo_off(R, f) * (T)0.0625;
+      if (r > (T)0.5) r -= (T)1;
+      T sn, cs;
+      sincos_rev(r, &sn, &cs);
+      w[f] = mk<T>(cs, sn);
+    }
+  } else {
+    cplx<T> pw[4];   // s, s^2, s^4, s^8
+    pw[0] = twiddle<T>(num, den);
+#pragma unroll
+    for (int k = 1; k < 4; ++k) pw[k] = mul(pw[k - 1], pw[k - 1]);
+    const T c1 = (T)0.92387953251128675613, s1 = (T)0.38268343236508977173, r2 = (T)0.70710678118654752440;
+    const cplx<T> root[4] = {mk<T>(1, 0), mk<T>(c1, s1), mk<T>(r2, r2), mk<T>(s1, c1)};   // w16^0..3
+#pragma unroll
+    for (int f = 0; f < geo_count(R); ++f) {
+      const int m = geo_mul(R, f), o = geo_off(R, f);
+      const cplx<T> b = pw[m == 1 ? 0 : m == 2 ? 1 : m == 4 ? 2 : 3];
+      w[f] = o ? mul(b, root[o]) : b;
+    }
   }
 }
 

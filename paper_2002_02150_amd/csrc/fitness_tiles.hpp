@@ -284,6 +284,96 @@ FCAS_HD void stage_gather(cplx<Real>* vs, const cplx<Real>* buf, int t) {
   for (int q = 0; q < E; ++q) vs[q] = buf[lds_pad<PAD>(t + q * P)];
 }
 
+// ---------------------------------------------------------------------------
+// The stages of the two main passes.  A thread's twiddle factors depend on
+// its place in the transform alone (pass 1), or on that and the row (pass 2),
+// so they are formed once and kept in registers while the thread takes one
+// point after the other (GeoSet).
+//
+// SHIFT transforms by x[k] exp(2 pi i k theta / L), theta = j1 / n1, first:
+// the four-step twiddle w_N^{k2 j1} of pass 2.  It needs no products of its
+// own: a stage of radix R after sub-length Ns then has the ratio
+//   s = exp(2 pi i ((v mod Ns) + theta) / (Ns R)).
+// ---------------------------------------------------------------------------
+template <int L, int E, class Rad, bool SHIFT>
+struct GeoShape {
+  static constexpr int P = L / E;
+  static constexpr int sub(int i) {   // product of the radices before stage i
+    int n = 1;
+    for (int k = 0; k < i; ++k) n *= Rad::value[k];
+    return n;
+  }
+  // butterflies of stage i with factors of their own (they share them where
+  // their places agree mod the sub-length)
+  static constexpr int sets(int i) { return P % sub(i) == 0 ? 1 : E / Rad::value[i]; }
+  static constexpr bool twiddled(int i) { return SHIFT || i > 0; }
+  static constexpr int offset(int i) {
+    int n = 0;
+    for (int k = 0; k < i; ++k)
+      if (twiddled(k)) n += sets(k) * geo_count(Rad::value[k]);
+    return n;
+  }
+  static constexpr int count = offset(Rad::count) > 0 ? offset(Rad::count) : 1;
+};
+
+template <typename Real, int L, int E, class Rad, bool SHIFT>
+struct GeoSet {
+  using Shape = GeoShape<L, E, Rad, SHIFT>;
+  cplx<Real> w[Shape::count];
+
+  // factors of thread t (of P per transform); SHIFT: for theta = j1 / n1
+  FCAS_HD void init(int t, int j1 = 0, int n1 = 1) { init_stage<0>(t, j1, n1); }
+
+  template <int I>
+  FCAS_HD void init_stage(int t, int j1, int n1) {
+    if constexpr (I < Rad::count) {
+      constexpr int R = Rad::value[I], Ns = Shape::sub(I);
+      if constexpr (Shape::twiddled(I)) {
+#pragma unroll
+        for (int b = 0; b < Shape::sets(I); ++b) {
+          const int v = (t + b * Shape::P) % Ns;
+          if constexpr (SHIFT)
+            geo_factors<R>(w + Shape::offset(I) + b * geo_count(R), v * n1 + j1, Ns * R * n1);
+          else
+            geo_factors<R>(w + Shape::offset(I) + b * geo_count(R), v, Ns * R);
+        }
+      }
+      init_stage<I + 1>(t, j1, n1);
+    }
+  }
+};
+
+// Stage I for one series of one transform: inputs in registers; outputs left
+// there (last stage) or scattered to the transform's LDS buffer.
+template <typename Real, int L, int E, class Rad, int I, bool SHIFT, bool HALF, int PAD>
+FCAS_HD void geo_stage(cplx<Real>* vs, cplx<Real>* buf, const GeoSet<Real, L, E, Rad, SHIFT>& g, int t) {
+  using Shape = GeoShape<L, E, Rad, SHIFT>;
+  constexpr int P = Shape::P, R = Rad::value[I], B = E / R, Ns = Shape::sub(I);
+  constexpr bool LAST = (I == Rad::count - 1);
+  static_assert(E % R == 0, "radix must divide the elements per thread");
+  static_assert(!HALF || (I == 0 && B == 1 && !SHIFT), "half-zero inputs only in an untwiddled first stage");
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    const int v = t + b * P;
+    cplx<Real> x[R];
+#pragma unroll
+    for (int p = 0; p < (HALF ? R / 2 : R); ++p) x[p] = vs[b + p * B];
+    if constexpr (HALF)
+      dft_half<R>(x);
+    else if constexpr (Shape::twiddled(I))
+      dft_geo<R>(x, g.w + Shape::offset(I) + (Shape::sets(I) == 1 ? 0 : b) * geo_count(R));
+    else
+      dft<R>(x);
+    if constexpr (LAST) {
+#pragma unroll
+      for (int p = 0; p < R; ++p) vs[b + p * B] = x[p];
+    } else {
+#pragma unroll
+      for (int p = 0; p < R; ++p) buf[lds_pad<PAD>(stockham_dst(v, Ns, R, p))] = x[p];
+    }
+  }
+}
+
 // Compile-time description of a plan.
 // Two-pass plans (NM = 1): N = N1 * N2,
 //   pass 1: C columns per work item, P1 = N1 / E1 threads per column
@@ -322,7 +412,7 @@ struct Plan {
   static constexpr int TILES1 = W1 / C, TILES2 = ROWS2 / RW;      // work items per evaluation
   static constexpr int TILESM = THREE ? N1 * (N2 / CM) : 0;
   static constexpr int DK1 = P1 * W1;                       // bin stride between a pass-1 thread's registers
-  static constexpr int PARTS2 = TILES2 * (T2 / 64);         // pass-2 partials (one per wavefront)
+  static constexpr int PARTS2 = TILES2;                     // pass-2 partials (one per work item)
   static_assert(Rad1::product() == N1, "pass-1 radices must multiply to N1");
   static_assert(Rad2::product() == N2, "pass-2 radices must multiply to N2");
   static_assert(RadM::product() == NM, "middle-pass radices must multiply to NM");
@@ -363,8 +453,7 @@ FCAS_HD int row_base(int row) {
 // reduced mod 1; r'_i is exact (FP64-reduced) at the thread's first bin and
 // advanced by the constant factor exp(2 pi i (P1 W1)(dly_i - dly_0)) of the
 // point's descriptor from register to register.  Out-of-band registers read
-// bin k_lo (any finite value) and are cleared by a zero e, so no lane
-// branches.
+// bin k_lo and are cleared once, so no lane branches.
 // ---------------------------------------------------------------------------
 // Segment data one pass-1 thread needs for a work item: y of its in-band
 // registers and detectors, and the basis b of those bins (DT > 0 only).
@@ -373,7 +462,6 @@ struct Pass1Data {
   static constexpr int QH = PL::E1 / 2;
   cplx<Real> y[DT > 0 ? DT : 1][QH];
   double b[QH];
-  bool in[QH];
   int k0;
 };
 
@@ -389,11 +477,14 @@ FCAS_HD void pass1_fetch(Pass1Data<Real, PL, DT>& d, const SegDesc& sg, int tile
 #pragma unroll
   for (int q = 0; q < QH; ++q) {
     const int k = d.k0 + q * DK;
-    d.in[q] = (k >= sg.k_lo) && (k <= sg.k_hi);
-    const int kk = d.in[q] ? k - sg.k_lo : 0;
+    const bool in = (k >= sg.k_lo) && (k <= sg.k_hi);
+    const int kk = in ? k - sg.k_lo : 0;
     d.b[q] = bt[kk];
 #pragma unroll
-    for (int i = 0; i < DT; ++i) d.y[i][q] = y[(int64_t)kk * DT + i];
+    for (int i = 0; i < DT; ++i) {
+      const cplx<Real> u = y[(int64_t)kk * DT + i];
+      d.y[i][q] = in ? u : mk<Real>(0, 0);
+    }
   }
 }
 
@@ -436,7 +527,7 @@ FCAS_HD Pass1Point<Real, DT> pass1_point(P ev) {
 // b, 0 otherwise (Ev: a descriptor with the phase coefficients `coef` and the
 // delay ramps `dly`).
 template <typename Real, class Ev>
-FCAS_HD cplx<Real> band_phase(const Ev& ev, double b, int k, bool in) {
+FCAS_HD cplx<Real> band_phase(const Ev& ev, double b, int k, bool in = true) {
   const double ph = common_phase(ev.coef, b) + (double)k * ev.dly[0];
   Real s, cc;
   sincos_rev((Real)(ph - rint(ph)), &s, &cc);
@@ -481,7 +572,7 @@ FCAS_HD void pass1_compute(cplx<Real> (&v)[2][PL::E1], const Pass1Data<Real, PL,
   }
 #pragma unroll
   for (int q = 0; q < QH; ++q) {
-    const cplx<Real> e = band_phase<Real>(ev, d.b[q], d.k0 + q * PL::DK1, d.in[q]);
+    const cplx<Real> e = band_phase<Real>(ev, d.b[q], d.k0 + q * PL::DK1);
     v[0][q] = mul(v[0][q], e);
     v[1][q] = mul(v[1][q], e);
   }
@@ -539,16 +630,18 @@ FCAS_HD void pass1_prologue(cplx<Real> (&v)[2][PL::E1], const EvalDesc& ev, cons
 
 // Pass 1 epilogue: store B[m][j1][k2] (the four-step twiddle is applied when
 // the next pass loads the rows).
-template <typename Real, class PL>
-FCAS_HD void pass1_store(cplx<Real> (&v)[2][PL::E1], cplx<Real>* slot, int tile, int c, int p) {
+template <typename Real, class PL, bool NT = false>
+FCAS_HD void pass1_store_series(cplx<Real> (&v)[PL::E1], cplx<Real>* slot, int s, int tile, int c, int p) {
   static_assert(2 * (int64_t)PL::N * sizeof(cplx<Real>) < (int64_t(1) << 31), "byte offsets fit in 31 bits");
   const StreamOut<Real> out(slot, 2 * (int64_t)PL::N);
   const int o = p * PL::W1 + tile * PL::C + c;      // row j1 = p, column k2
 #pragma unroll
-  for (int q = 0; q < PL::E1; ++q) {
-    out.store(o, q * PL::P1 * PL::W1, v[0][q]);       // row j1 = p + q P1
-    out.store(o, PL::N + q * PL::P1 * PL::W1, v[1][q]);
-  }
+  for (int q = 0; q < PL::E1; ++q) out.template store<NT>(o, s * (int)PL::N + q * PL::P1 * PL::W1, v[q]);   // row p + q P1
+}
+template <typename Real, class PL, bool NT = false>
+FCAS_HD void pass1_store(cplx<Real> (&v)[2][PL::E1], cplx<Real>* slot, int tile, int c, int p) {
+  pass1_store_series<Real, PL, NT>(v[0], slot, 0, tile, c, p);
+  pass1_store_series<Real, PL, NT>(v[1], slot, 1, tile, c, p);
 }
 
 // ---------------------------------------------------------------------------
@@ -662,37 +755,33 @@ FCAS_HD void pass2_load(cplx<Real> (&v)[2][PL::E2], const cplx<Real>* slot, int 
   if constexpr (!PL::THREE) pass2_twiddle<Real, PL>(v, tile, r, p);
 }
 
-// Pass 2 epilogue: Gamma^2_j = |a_0|^2 + |a_1|^2 at j = row_base + ROWS2 (p + q P2),
+// Pass 2 epilogue: Gamma^2_j = |a_0|^2 + |a_1|^2 (g) at j = row_base + ROWS2 (p + q P2),
 // for j_lo <= j < j_hi; the thread's largest value and, among equal values,
 // its smallest j (value -1 if none of its samples is in range).
 template <typename Real, class PL>
-FCAS_HD void pass2_best(const cplx<Real> (&v)[2][PL::E2], int tile, int r, int p, Real& best, int& best_j,
-                        int64_t j_lo = 0, int64_t j_hi = PL::N) {
+FCAS_HD void pass2_best_of(const Real (&g)[PL::E2], int tile, int r, int p, Real& best, int& best_j, int64_t j_lo,
+                           int64_t j_hi) {
   const int j0 = row_base<PL>(tile * PL::RW + r);
   const int lo = j_lo > 0 ? (int)j_lo : 0;
   const int hi = j_hi < PL::N ? (int)j_hi : (int)PL::N;
   best = (Real)-1;
   best_j = 0x7fffffff;
-  if (lo == 0 && hi == (int)PL::N) {   // whole series (uniform branch)
 #pragma unroll
-    for (int q = 0; q < PL::E2; ++q) {
-      const Real g = norm2(v[0][q]) + norm2(v[1][q]);
-      if (g > best) {   // j grows with q: ties keep the smaller j
-        best = g;
-        best_j = j0 + PL::ROWS2 * (p + q * PL::P2);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < PL::E2; ++q) {
-      const Real g = norm2(v[0][q]) + norm2(v[1][q]);
-      const int j = j0 + PL::ROWS2 * (p + q * PL::P2);
-      if (g > best && j >= lo && j < hi) {
-        best = g;
-        best_j = j;
-      }
+  for (int q = 0; q < PL::E2; ++q) {
+    const int j = j0 + PL::ROWS2 * (p + q * PL::P2);
+    if (g[q] > best && j >= lo && j < hi) {   // j grows with q: ties keep the smaller j
+      best = g[q];
+      best_j = j;
     }
   }
+}
+template <typename Real, class PL>
+FCAS_HD void pass2_best(const cplx<Real> (&v)[2][PL::E2], int tile, int r, int p, Real& best, int& best_j,
+                        int64_t j_lo = 0, int64_t j_hi = PL::N) {
+  Real g[PL::E2];
+#pragma unroll
+  for (int q = 0; q < PL::E2; ++q) g[q] = norm2(v[0][q]) + norm2(v[1][q]);
+  pass2_best_of<Real, PL>(g, tile, r, p, best, best_j, j_lo, j_hi);
 }
 
 // Work item `item` of the fused schedule (cnt evaluations, lag L, T1 pass-1

@@ -31,6 +31,10 @@ hipError_t launch_setup(const NetDesc* net, const SegDesc* segs, const double* t
 hipError_t launch_fused_f32(int plan, const FusedArgs& f, int grid, hipStream_t s);
 int fused_blocks_per_cu(int plan);
 
+// pass 1 of one precision and detector count (eval_pass1.hip, one object each)
+template <typename Real, int DT>
+hipError_t launch_pass1_dt(int plan, const PassArgs& a, int grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
+
 // precision: 0 float, 1 double; e0 / e1: optional timing events (launch_k)
 hipError_t launch_pass1(int precision, int plan, const PassArgs& a, int grid, hipStream_t s, hipEvent_t e0 = nullptr,
                         hipEvent_t e1 = nullptr);
@@ -38,7 +42,7 @@ hipError_t launch_passm(int precision, int plan, const PassArgs& a, int grid, hi
                         hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 hipError_t launch_pass2(int precision, int plan, const PassArgs& a, int grid, hipStream_t s, hipEvent_t e0 = nullptr,
                         hipEvent_t e1 = nullptr);
-hipError_t launch_finalize(int precision, const EvalDesc* evals, const SegDesc* segs, const void* part_g,
+hipError_t launch_finalize(int precision, const EvalDesc* evals, const void* part_g,
                            const int32_t* part_j, int n, int part_stride, const int32_t* plan_parts2,
                            int32_t* counts, unsigned long long* evaluated, double* fitness, int32_t* argmax,
                            hipStream_t s);

@@ -1,7 +1,9 @@
 // plans.hpp -- FFT plans of the supported segment lengths.
 //
 // N = N1 * N2 with N1 the pass-1 (column) length and N2 the pass-2 (row)
-// length; radix-3 lengths (3 * 2^k) put the factor 3 in the length-768 rows.
+// length; the lengths 3 * 2^k put the factor 3 in the columns, whose first
+// stage is a 12-point transform, and keep rows of 512 points, which one
+// wavefront transforms by itself.
 // Lengths 2^k * 225 (whole minutes at 2048 Hz from 225 s up) add a middle
 // pass of length NM = 225 = 15 * 15 between them (N = N1 * NM * N2).
 // Work items hold 256 threads for float; the double variants halve the
@@ -12,11 +14,10 @@
 
 namespace fcas {
 
-// Pass 2 leaves one partial (maximum, sample) per wavefront of each work item:
-// TILES2 * T2 / 64 per evaluation, at most kMaxParts2 over all plans.  A
-// context sizes its partial buffers by the largest count among the plans its
+// Pass 2 leaves one partial (maximum, sample) per work item: TILES2 per
+// evaluation, at most kMaxParts2 over all plans.  A context sizes its partial buffers by the largest count among the plans its
 // maximum segment length admits.
-constexpr int kMaxParts2 = 16384;
+constexpr int kMaxParts2 = 4096;
 
 template <int... R>
 using Rad = Radices<R...>;
@@ -26,27 +27,27 @@ using Rad = Radices<R...>;
   /*  id     N      N1 E1 rad1          C(f) C(d)  N2  E2 rad2             RW(f) RW(d)  NM EM radM CM(f) CM(d) */ \
   X(0,   2048,     32, 8, (8, 4),       64, 64,   64, 8, (8, 8),          32, 32, 1, 1, (1), 1, 1) \
   X(1,   4096,     64, 8, (8, 8),       32, 32,   64, 8, (8, 8),          32, 32, 1, 1, (1), 1, 1) \
-  X(2,   8192,     64, 8, (8, 8),       32, 32,  128, 16, (16, 8),        32, 16, 1, 1, (1), 1, 1) \
-  X(3,  16384,    128, 16, (16, 8),     32, 16,  128, 16, (16, 8),        32, 16, 1, 1, (1), 1, 1) \
-  X(4,  32768,    128, 16, (16, 8),     32, 16,  256, 16, (16, 16),       16, 8, 1, 1, (1), 1, 1) \
-  X(5,  65536,    256, 16, (16, 16),    16, 8,   256, 16, (16, 16),       16, 8, 1, 1, (1), 1, 1) \
-  X(6, 131072,    256, 16, (16, 16),    16, 8,   512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
-  X(7, 262144,    512, 16, (16, 16, 2), 8, 4,    512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
-  X(8,  24576,     32, 8, (8, 4),       64, 64,  768, 24, (8, 8, 4, 3),   8, 4, 1, 1, (1), 1, 1) \
-  X(9,  49152,     64, 8, (8, 8),       32, 32,  768, 24, (8, 8, 4, 3),   8, 4, 1, 1, (1), 1, 1) \
-  X(10, 98304,    128, 16, (16, 8),     32, 16,  768, 24, (8, 8, 4, 3),   8, 4, 1, 1, (1), 1, 1) \
-  X(11, 196608,   256, 16, (16, 16),    16, 8,   768, 24, (8, 8, 4, 3),   8, 4, 1, 1, (1), 1, 1) \
+  X(2,   8192,     16, 8, (8, 2),      128, 64,  512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
+  X(3,  16384,     32, 8, (8, 4),       64, 32,  512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
+  X(4,  32768,     64, 8, (8, 8),       32, 16,  512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
+  X(5,  65536,    128, 8, (8, 8, 2),    16, 16,  512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
+  X(6, 131072,    256, 8, (8, 8, 4),    16, 8,   512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
+  X(7, 262144,    256, 8, (8, 8, 4),    16, 8,  1024, 16, (16, 8, 8),     4, 2, 1, 1, (1), 1, 1) \
+  X(8,  24576,     48, 12, (12, 4),     64, 32,  512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
+  X(9,  49152,     96, 12, (12, 4, 2),  32, 16,  512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
+  X(10, 98304,    192, 12, (12, 4, 4),  16, 8,   512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
+  X(11, 196608,   384, 12, (12, 4, 4, 2), 8, 8,  512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
   /* alternatives, picked per device by the autotuner */                                            \
-  X(12, 131072,   128, 16, (16, 8),     32, 16, 1024, 16, (16, 16, 4),    4, 2, 1, 1, (1), 1, 1) \
-  X(13, 131072,   256, 16, (16, 16),    16, 8,   512, 16, (16, 16, 2),    8, 4, 1, 1, (1), 1, 1) \
-  X(14, 131072,   512, 16, (16, 16, 2), 8, 4,    256, 16, (16, 16),       16, 8, 1, 1, (1), 1, 1) \
+  X(12, 131072,   128, 8, (8, 4, 4),    16, 16, 1024, 16, (16, 8, 8),     4, 2, 1, 1, (1), 1, 1) \
+  X(13, 131072,   256, 16, (16, 16),    16, 8,   512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
+  X(14, 131072,   512, 8, (8, 8, 8),    8, 8,    256, 8, (8, 8, 4),       8, 8, 1, 1, (1), 1, 1) \
   X(15, 131072,   256, 8, (8, 8, 4),    8, 8,    512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
-  X(16, 262144,   256, 16, (16, 16),    16, 8,  1024, 16, (16, 16, 4),    4, 2, 1, 1, (1), 1, 1) \
-  X(17,  65536,   128, 16, (16, 8),     32, 16,  512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
-  X(18, 196608,   256, 16, (16, 16),    16, 8,   768, 12, (4, 4, 4, 4, 3), 4, 4, 1, 1, (1), 1, 1) \
-  X(19,   8192,   128, 16, (16, 8),     32, 16,   64, 8, (8, 8),          32, 16, 1, 1, (1), 1, 1) \
+  X(16, 262144,   512, 16, (16, 16, 2), 16, 4,   512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
+  X(17,  65536,    64, 8, (8, 8),       32, 16, 1024, 16, (16, 8, 8),     4, 2, 1, 1, (1), 1, 1) \
+  X(18, 196608,   384, 12, (12, 4, 4, 2), 16, 8, 512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
+  X(19,   8192,    64, 8, (8, 8),       32, 16,  128, 8, (8, 4, 4),       16, 8, 1, 1, (1), 1, 1) \
   X(20, 262144,   256, 8, (8, 8, 4),    8, 8,   1024, 8, (8, 8, 8, 2),    2, 2, 1, 1, (1), 1, 1) \
-  X(21, 196608,   256, 8, (8, 8, 4),    8, 8,    768, 12, (4, 4, 4, 4, 3), 4, 4, 1, 1, (1), 1, 1) \
+  X(21, 196608,   192, 12, (12, 4, 4),  16, 8,  1024, 16, (16, 8, 8),     4, 2, 1, 1, (1), 1, 1) \
   X(22,  65536,   256, 8, (8, 8, 4),    8, 8,    256, 8, (8, 8, 4),       8, 8, 1, 1, (1), 1, 1) \
   X(23,  65536,   128, 8, (8, 4, 4),    16, 16,  512, 8, (8, 8, 8),       4, 4, 1, 1, (1), 1, 1) \
   X(24, 131072,   128, 8, (8, 4, 4),    16, 16, 1024, 8, (8, 8, 8, 2),    2, 2, 1, 1, (1), 1, 1) \

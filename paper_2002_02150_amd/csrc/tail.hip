@@ -34,8 +34,8 @@ __global__ void __launch_bounds__(kTailMaxThreads) k_pso_tail(PsoDev p, TailArgs
     if (c) atomicAdd(t.evaluated, (unsigned long long)c);
   }
   if (k < P)
-    finalize_group<Real>(t.evals[base + k], (const Real*)t.part_g, t.part_j, t.part_stride, t.plan_parts2,
-                         base + k, tid & 7, t.fitness, t.argmax);
+    finalize_group<Real, 8>(t.evals[base + k], (const Real*)t.part_g, t.part_j, t.part_stride, t.plan_parts2,
+                            base + k, tid & 7, t.fitness, t.argmax);
   __syncthreads();   // the run's fitness, written by its groups, is read by the swarm update
   pso_step_run(p, L, t.fitness, t.argmax, t.theta, PsoShared{s_pf, s_px, s_pj}, s_theta, r, tid);
   if (!t.setup) return;
