@@ -530,28 +530,39 @@ __device__ __forceinline__ void finalize_group(const EvalDesc& ev, const Real* _
                                                const int32_t* __restrict__ part_j, int part_stride,
                                                const int32_t* __restrict__ plan_parts2, int e, int g,
                                                double* __restrict__ fitness, int32_t* __restrict__ argmax) {
+  constexpr int B = G >= 64 ? 2 : 8;   // loads per lane in flight before any is compared
+  const Real* pg = part_g + (int64_t)e * part_stride;
+  const int32_t* pj = part_j + (int64_t)e * part_stride;
+  // the first batch is read together with the descriptor, whether or not the
+  // point has left that many partials
+  Real gv[B];
+  int jv[B];
+#pragma unroll
+  for (int u = 0; u < B; ++u) {
+    const int t = g + G * u < part_stride ? g + G * u : 0;
+    gv[u] = pg[t];
+    jv[u] = pj[t];
+  }
   const int status = ev.status;
   Real bg = (Real)-1;
   int bj = 0x7fffffff;
   if (status == 1) {
     const int nt = plan_parts2[ev.plan];
-    // batches of B loads per lane in flight before any is compared
-    constexpr int B = G >= 64 ? 8 : 16;
-    for (int t0 = g; t0 < nt; t0 += G * B) {
-      Real gv[B];
-      int jv[B];
-#pragma unroll
-      for (int u = 0; u < B; ++u) {
-        const int t = t0 + G * u;
-        gv[u] = t < nt ? part_g[(int64_t)e * part_stride + t] : (Real)-1;
-        jv[u] = t < nt ? part_j[(int64_t)e * part_stride + t] : 0x7fffffff;
-      }
+    for (int t0 = g;;) {
 #pragma unroll
       for (int u = 0; u < B; ++u)
-        if (better(gv[u], jv[u], bg, bj)) {
+        if (t0 + G * u < nt && better(gv[u], jv[u], bg, bj)) {
           bg = gv[u];
           bj = jv[u];
         }
+      t0 += G * B;
+      if (t0 - g >= nt) break;
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int t = t0 + G * u < nt ? t0 + G * u : 0;
+        gv[u] = pg[t];
+        jv[u] = pj[t];
+      }
     }
 #pragma unroll
     for (int off = G / 2; off > 0; off >>= 1) {

@@ -80,17 +80,15 @@ constexpr double kC = 299792458.0;
 // Written once for two executions: `Dets` is either a loop over the
 // detectors (setup_one, one thread per point) or a group of lanes with one
 // detector each, whose sums over detectors are lane reductions (the kernel).
-// Per-detector values live in the point's descriptor; a lane only ever reads
-// back the entries it wrote itself.
+// A detector's values stay in registers (DetPoint) until the descriptor is
+// written.
 // ---------------------------------------------------------------------------
 struct SkyFrame {
   double n[3], ex[3], ey[3];   // propagation direction and wave axes (-alpha_hat, delta_hat)
 };
 
-// Phase coefficients (cycles) and the sky frame of a point.
-FCAS_HD void setup_point(const NetDesc& net, const double* th, double coef[4], SkyFrame& fr) {
-  const double alpha = th[0], delta = th[1], tau0 = th[2], tau15 = th[3];
-  const double fs = net.f_star;
+// Phase coefficients (cycles) of a point.
+FCAS_HD void setup_phase(double tau0, double tau15, double fs, double coef[4]) {
   const double v0 = cbrt(5.0 * tau15 / (32.0 * kPi * tau0));
   const double eta = 1.0 / (8.0 * fs * tau15 * v0 * v0);
   const double tau1 = 5.0 / (192.0 * kPi * fs * eta * v0 * v0 * v0) * (743.0 / 336.0 + 11.0 * eta / 4.0);
@@ -100,12 +98,21 @@ FCAS_HD void setup_point(const NetDesc& net, const double* th, double coef[4], S
   coef[1] = fs * tau1;
   coef[2] = -fs * 1.5 * tau15;
   coef[3] = fs * 3.0 * tau2;
-  double sa, ca, sd, cd;
-  sincos(alpha, &sa, &ca);
-  sincos(delta, &sd, &cd);
+}
+
+// The sky frame from the sines and cosines of alpha and delta.
+FCAS_HD void setup_sky(double sa, double ca, double sd, double cd, SkyFrame& fr) {
   fr.n[0] = cd * ca; fr.n[1] = cd * sa; fr.n[2] = sd;
   fr.ex[0] = sa; fr.ex[1] = -ca; fr.ex[2] = 0.0;
   fr.ey[0] = -sd * ca; fr.ey[1] = -sd * sa; fr.ey[2] = cd;
+}
+
+FCAS_HD void setup_point(const NetDesc& net, const double* th, double coef[4], SkyFrame& fr) {
+  setup_phase(th[2], th[3], net.f_star, coef);
+  double sa, ca, sd, cd;
+  sincos(th[0], &sa, &ca);
+  sincos(th[1], &sd, &cd);
+  setup_sky(sa, ca, sd, cd, fr);
 }
 
 // Delay ramp of detector i in cycles per bin of width df (delay relative to
@@ -115,88 +122,103 @@ FCAS_HD double detector_delay(const NetDesc& net, double df, const SkyFrame& fr,
   return -(fr.n[0] * r[0] + fr.n[1] * r[1] + fr.n[2] * r[2]) / kC * df;
 }
 
-// Detector i of a segment with bin width df, pass-1 register stride dk1 and
-// template norm sigma_i: delay ramp (cycles per bin), its pass-1 step
-// relative to detector 0, and row i of V.
-FCAS_HD void setup_detector(const NetDesc& net, double df, int dk1, double sigma_i, const SkyFrame& fr, int i,
-                            EvalDesc& ev) {
-  ev.dly[i] = detector_delay(net, df, fr, i);
-  const double ps = (double)dk1 * (ev.dly[i] - detector_delay(net, df, fr, 0));
-  double ss, cs;
-  sincos_rev(ps - rint(ps), &ss, &cs);
-  ev.step1[i][0] = cs;
-  ev.step1[i][1] = ss;
-  ev.step1f[i][0] = (float)cs;
-  ev.step1f[i][1] = (float)ss;
+// What the set-up computes of one detector.
+struct DetPoint {
+  double dly;        // delay ramp, cycles per bin
+  double step[2];    // its pass-1 step relative to detector 0
+  double v[2];       // row of V
+  double q[2];       // row of Q
+};
+
+// Delay ramp and row of V of detector i, of a segment with bin width df and
+// template norm sigma_i.
+FCAS_HD void setup_detector(const NetDesc& net, double df, double sigma_i, const SkyFrame& fr, int i, DetPoint& d) {
+  d.dly = detector_delay(net, df, fr, i);
   double up = 0.0, uc = 0.0;
   for (int a = 0; a < 3; ++a)
     for (int b = 0; b < 3; ++b) {
-      const double d = net.ten[i][a][b];
-      up += d * (fr.ex[a] * fr.ex[b] - fr.ey[a] * fr.ey[b]);
-      uc += d * (fr.ex[a] * fr.ey[b] + fr.ey[a] * fr.ex[b]);
+      const double t = net.ten[i][a][b];
+      up += t * (fr.ex[a] * fr.ex[b] - fr.ey[a] * fr.ey[b]);
+      uc += t * (fr.ex[a] * fr.ey[b] + fr.ey[a] * fr.ex[b]);
     }
-  ev.v[i][0] = sigma_i * up;
-  ev.v[i][1] = sigma_i * uc;
+  d.v[0] = sigma_i * up;
+  d.v[1] = sigma_i * uc;
+}
+
+// Its ramp across one pass-1 register stride of dk1 bins, relative to
+// detector 0's delay ramp dly0.
+FCAS_HD void setup_step(int dk1, double dly0, DetPoint& d) {
+  const double ps = (double)dk1 * (d.dly - dly0);
+  sincos_rev(ps - rint(ps), &d.step[1], &d.step[0]);
 }
 
 // Orthonormal basis Q of span(V): modified Gram-Schmidt, twice, larger
-// column first; q[i][1] holds the residual of the second column until it is
+// column first; q[1] holds the residual of the second column until it is
 // normalised.  Returns the rank (0, 1 or 2).
 template <class Dets>
-FCAS_HD int setup_basis(EvalDesc& ev, const Dets& dets) {
-  const double n0 = dets.sum([&](int i) { return ev.v[i][0] * ev.v[i][0]; });
-  const double n1 = dets.sum([&](int i) { return ev.v[i][1] * ev.v[i][1]; });
+FCAS_HD int setup_basis(Dets& dets) {
+  const double n0 = dets.sum([](const DetPoint& d) { return d.v[0] * d.v[0]; });
+  const double n1 = dets.sum([](const DetPoint& d) { return d.v[1] * d.v[1]; });
   const double vf = n0 + n1;
-  const int ca = (n1 > n0) ? 1 : 0, cb = 1 - ca;
-  const double na = sqrt(ca ? n1 : n0);
-  dets.all([&](int i) { ev.q[i][0] = ev.q[i][1] = 0.0; });
+  const bool second = n1 > n0;   // the larger column
+  const double na = sqrt(second ? n1 : n0);
+  dets.each([](DetPoint& d) { d.q[0] = d.q[1] = 0.0; });
   int rank = 0;
   if (na > 0.0) {
     rank = 1;
-    dets.each([&](int i) {
-      ev.q[i][0] = ev.v[i][ca] / na;
-      ev.q[i][1] = ev.v[i][cb];
+    dets.each([&](DetPoint& d) {
+      d.q[0] = (second ? d.v[1] : d.v[0]) / na;
+      d.q[1] = second ? d.v[0] : d.v[1];
     });
     for (int pass = 0; pass < 2; ++pass) {
-      const double dot = dets.sum([&](int i) { return ev.q[i][0] * ev.q[i][1]; });
-      dets.each([&](int i) { ev.q[i][1] -= dot * ev.q[i][0]; });
+      const double dot = dets.sum([](const DetPoint& d) { return d.q[0] * d.q[1]; });
+      dets.each([&](DetPoint& d) { d.q[1] -= dot * d.q[0]; });
     }
-    const double nb = sqrt(dets.sum([&](int i) { return ev.q[i][1] * ev.q[i][1]; }));
-    if (nb > 1e-10 * sqrt(vf)) {
-      rank = 2;
-      dets.each([&](int i) { ev.q[i][1] /= nb; });
-    } else {
-      dets.each([&](int i) { ev.q[i][1] = 0.0; });
-    }
+    const double nb = sqrt(dets.sum([](const DetPoint& d) { return d.q[1] * d.q[1]; }));
+    const bool full = nb > 1e-10 * sqrt(vf);
+    if (full) rank = 2;
+    dets.each([&](DetPoint& d) { d.q[1] = full ? d.q[1] / nb : 0.0; });
   }
-  dets.all([&](int i) {
-    ev.qf[i][0] = (float)ev.q[i][0];
-    ev.qf[i][1] = (float)ev.q[i][1];
-  });
   return rank;
+}
+
+// Detector i's entries of a point's descriptor.
+FCAS_HD void store_detector(EvalDesc& ev, int i, const DetPoint& d) {
+  ev.dly[i] = d.dly;
+  for (int m = 0; m < 2; ++m) {
+    ev.v[i][m] = d.v[m];
+    ev.q[i][m] = d.q[m];
+    ev.qf[i][m] = (float)d.q[m];
+    ev.step1[i][m] = d.step[m];
+    ev.step1f[i][m] = (float)d.step[m];
+  }
 }
 
 // The detectors as a loop of one thread.
 struct DetLoop {
   int n_det;
+  DetPoint p[kMaxDet];
   template <class F> FCAS_HD double sum(F f) const {
     double acc = 0.0;
-    for (int i = 0; i < n_det; ++i) acc += f(i);
+    for (int i = 0; i < n_det; ++i) acc += f(p[i]);
     return acc;
   }
-  template <class F> FCAS_HD void each(F f) const {
-    for (int i = 0; i < n_det; ++i) f(i);
-  }
-  template <class F> FCAS_HD void all(F f) const {   // every descriptor slot, used or not
-    for (int i = 0; i < kMaxDet; ++i) f(i);
+  template <class F> FCAS_HD void each(F f) {
+    for (int i = 0; i < n_det; ++i) f(p[i]);
   }
 };
 
 FCAS_HD void setup_one(const NetDesc& net, const SegDesc& sg, const double* th, EvalDesc& ev) {
   SkyFrame fr;
   setup_point(net, th, ev.coef, fr);
-  for (int i = 0; i < net.n_det; ++i) setup_detector(net, sg.df, sg.dk1, sg.sigma[i], fr, i, ev);
-  ev.rank = setup_basis(ev, DetLoop{net.n_det});
+  DetLoop dets{};
+  dets.n_det = net.n_det;
+  for (int i = 0; i < net.n_det; ++i) {
+    setup_detector(net, sg.df, sg.sigma[i], fr, i, dets.p[i]);
+    setup_step(sg.dk1, dets.p[0].dly, dets.p[i]);
+  }
+  ev.rank = setup_basis(dets);
+  for (int i = 0; i < net.n_det; ++i) store_detector(ev, i, dets.p[i]);
 }
 
 // Common phase of bin k in cycles, b = (f_k / f*)^(-1/3): FP64 throughout.

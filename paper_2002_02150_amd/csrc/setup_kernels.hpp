@@ -8,22 +8,34 @@
 
 namespace fcas {
 
+// A double from the lane that a DPP control names.
+template <int CTRL>
+__device__ __forceinline__ double dpp_double(double x) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// Sum over an aligned group of 8 lanes, in every lane: pairs, quads (both quad
+// permutations), then the two quads (each lane reads its mirror image in the
+// group of 8).  The same additions as a butterfly of shuffles, without the
+// LDS round trip of each.
+__device__ __forceinline__ double sum8(double x) {
+  x += dpp_double<0xb1>(x);    // quad_perm 1,0,3,2
+  x += dpp_double<0x4e>(x);    // quad_perm 2,3,0,1
+  x += dpp_double<0x141>(x);   // row_half_mirror
+  return x;
+}
+
 // The detectors of one point as a group of 8 lanes, lane g holding detector g;
-// sums over detectors are butterfly reductions inside the group (every lane
-// gets the same, order-independent total: IEEE addition commutes).
+// sums over detectors are butterfly reductions inside the group of eight
+// (every lane gets the same, order-independent total: IEEE addition commutes).
 struct DetLanes {
-  int n_det, g;
-  template <class F> __device__ double sum(F f) const {
-    double x = g < n_det ? f(g) : 0.0;
-    x += __shfl_xor(x, 1, 8);
-    x += __shfl_xor(x, 2, 8);
-    x += __shfl_xor(x, 4, 8);
-    return x;
-  }
-  template <class F> __device__ void each(F f) const {
-    if (g < n_det) f(g);
-  }
-  template <class F> __device__ void all(F f) const { f(g); }
+  bool on;       // this lane holds a detector
+  DetPoint p;
+  template <class F> __device__ double sum(F f) const { return sum8(on ? f(p) : 0.0); }
+  template <class F> __device__ void each(F f) { f(p); }
 };
 static_assert(kMaxDet == 8, "one lane per detector slot in a group of 8");
 
@@ -81,9 +93,21 @@ __device__ __forceinline__ void setup_group(const NetDesc& net, const SetupSeg& 
       if (inside) {
         double coef[4];
         SkyFrame fr;
-        setup_point(net, th, coef, fr);
-        if (g < net.n_det) setup_detector(net, q.df, q.dk1, q.sigma_g, fr, g, ev);
-        const int rank = setup_basis(ev, DetLanes{net.n_det, g});
+        setup_phase(th[2], th[3], net.f_star, coef);
+        // one sine and cosine for both angles: odd lanes take delta's
+        double s1, c1;
+        sincos(th[g & 1], &s1, &c1);
+        const double s2 = dpp_double<0xb1>(s1), c2 = dpp_double<0xb1>(c1);
+        setup_sky(g & 1 ? s2 : s1, g & 1 ? c2 : c1, g & 1 ? s1 : s2, g & 1 ? c1 : c2, fr);
+        DetLanes dets{};
+        dets.on = g < net.n_det;
+        setup_detector(net, q.df, q.sigma_g, fr, dets.on ? g : 0, dets.p);
+        // detector 0's delay ramp, from lane 0 of the group (by its quad, then
+        // the other quad's mirror image)
+        const double d0 = dpp_double<0x00>(dets.p.dly), d1 = dpp_double<0x141>(d0);
+        setup_step(q.dk1, g < 4 ? d0 : d1, dets.p);
+        const int rank = setup_basis(dets);
+        if (dets.on) store_detector(ev, g, dets.p);
         if (g == 0) {
           for (int k = 0; k < 4; ++k) ev.coef[k] = coef[k];
           ev.rank = rank;
