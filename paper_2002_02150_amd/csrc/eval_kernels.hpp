@@ -526,10 +526,10 @@ __global__ void __launch_bounds__(PL::T2)
 // result.
 // ---------------------------------------------------------------------------
 template <typename Real, int G>
-__device__ __forceinline__ void finalize_group(const EvalDesc& ev, const Real* __restrict__ part_g,
+__device__ __forceinline__ void finalize_value(const EvalDesc& ev, const Real* __restrict__ part_g,
                                                const int32_t* __restrict__ part_j, int part_stride,
-                                               const int32_t* __restrict__ plan_parts2, int e, int g,
-                                               double* __restrict__ fitness, int32_t* __restrict__ argmax) {
+                                               const int32_t* __restrict__ plan_parts2, int e, int g, double& fitness,
+                                               int& argmax) {
   constexpr int B = G >= 64 ? 2 : 8;   // loads per lane in flight before any is compared
   const Real* pg = part_g + (int64_t)e * part_stride;
   const int32_t* pj = part_j + (int64_t)e * part_stride;
@@ -574,9 +574,22 @@ __device__ __forceinline__ void finalize_group(const EvalDesc& ev, const Real* _
       }
     }
   }
+  fitness = status == 1 ? (double)bg : status == 0 ? -INFINITY : NAN;
+  argmax = status == 1 ? bj : status == 0 ? -1 : -2;
+}
+
+// The same, written to the call's outputs.
+template <typename Real, int G>
+__device__ __forceinline__ void finalize_group(const EvalDesc& ev, const Real* __restrict__ part_g,
+                                               const int32_t* __restrict__ part_j, int part_stride,
+                                               const int32_t* __restrict__ plan_parts2, int e, int g,
+                                               double* __restrict__ fitness, int32_t* __restrict__ argmax) {
+  double f;
+  int j;
+  finalize_value<Real, G>(ev, part_g, part_j, part_stride, plan_parts2, e, g, f, j);
   if (g == 0) {
-    fitness[e] = status == 1 ? (double)bg : status == 0 ? -INFINITY : NAN;
-    argmax[e] = status == 1 ? bj : status == 0 ? -1 : -2;
+    fitness[e] = f;
+    argmax[e] = j;
   }
 }
 

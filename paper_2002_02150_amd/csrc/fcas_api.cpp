@@ -112,11 +112,8 @@ struct fcas_ctx {
   size_t ws_bytes = 0;
   void* d_scratch = nullptr;     // this device's copy of the static scratch array (not owned)
   GradBuffers grad{};
-  double* d_pol_grad = nullptr;    // [max_batch][4] polish: gradient at the current points
+  EvalDesc* d_pol_evals = nullptr; // [max_batch] polish: descriptors of the current points
   double* d_pol_cand = nullptr;    // [max_batch][4] polish trials
-  int32_t* d_pol_seg = nullptr;    // [max_batch]
-  double* d_pol_f = nullptr;       // [max_batch]
-  int32_t* d_pol_j = nullptr;      // [max_batch]
   int plan_refs[kNumPlans] = {0};   // registered segments per plan
   int schedule = FCAS_SCHEDULE_FUSED;
   int n_cu = 0;                     // compute units of the device
@@ -195,7 +192,7 @@ int free_all(fcas_ctx* c) {
   for (double* p : c->seg_b) if (p) hipFree(p);
   void* bufs[] = {c->d_net, c->d_segs, c->d_evals, c->d_lists, c->d_counts, c->d_part_g,
                   c->d_part_j, c->d_plan_parts2, c->d_err, c->d_sigma2, c->d_inject, c->d_ws,
-                  c->d_pol_grad, c->d_pol_cand, c->d_pol_seg, c->d_pol_f, c->d_pol_j, c->d_evaluated,
+                  c->d_pol_evals, c->d_pol_cand, c->d_evaluated,
                   c->d_done, c->d_lists2, c->d_counts2};
   for (void* p : bufs) if (p) hipFree(p);
   free_grad_buffers(c->grad);
@@ -321,10 +318,8 @@ int fcas_create(const fcas_network* net, const fcas_config* cfg, int device, fca
       (rc = dev_alloc(&c->d_err, sizeof(int32_t))) || (rc = dev_alloc(&c->d_sigma2, sizeof(double) * FCAS_MAX_DET)) ||
       (rc = dev_alloc(&c->d_inject, sizeof(double) * kInjectScratch)) ||
       (rc = dev_alloc(&c->d_ws, ws)) || (rc = alloc_grad_buffers(c->grad, B, net->n_det)) ||
-      (rc = dev_alloc(&c->d_pol_grad, sizeof(double) * 4 * B)) ||
+      (rc = dev_alloc(&c->d_pol_evals, sizeof(EvalDesc) * B)) ||
       (rc = dev_alloc(&c->d_pol_cand, sizeof(double) * 4 * B)) ||
-      (rc = dev_alloc(&c->d_pol_seg, sizeof(int32_t) * B)) || (rc = dev_alloc(&c->d_pol_f, sizeof(double) * B)) ||
-      (rc = dev_alloc(&c->d_pol_j, sizeof(int32_t) * B)) ||
       (rc = dev_alloc(&c->d_evaluated, sizeof(unsigned long long))) ||
       (rc = dev_alloc(&c->d_done, sizeof(int32_t) * 2 * (size_t)kNumPlans * B))) {
     std::string msg = g_last_error;
@@ -745,7 +740,7 @@ int fitness_polish(fcas_ctx* ctx, int32_t n, double* d_theta, const int32_t* d_s
                    double step_frac, int32_t n_trials, double* d_fitness, int32_t* d_argmax, void* hip_stream) {
   int rc = validate_batch(ctx, n, d_theta, d_seg, d_fitness, d_argmax);
   if (rc) return rc;
-  if (n_steps < 0 || n_trials < 1 || n_trials > 32) return fail(FCAS_EINVAL, "need n_steps >= 0, 1 <= n_trials <= 32");
+  if (n_steps < 0 || n_trials < 1 || n_trials > kMaxTrials) return fail(FCAS_EINVAL, "need n_steps >= 0, 1 <= n_trials <= 32");
   if (!(step_frac > 0) || !std::isfinite(step_frac)) return fail(FCAS_EINVAL, "step_frac must be positive");
   if ((int64_t)n * n_trials > ctx->cfg.max_batch)
     return fail(FCAS_ECAPACITY, "n * n_trials = %lld exceeds max_batch = %d", (long long)n * n_trials,
@@ -754,24 +749,29 @@ int fitness_polish(fcas_ctx* ctx, int32_t n, double* d_theta, const int32_t* d_s
   hipSetDevice(ctx->device);
   hipStream_t s = (hipStream_t)hip_stream;
   hipError_t e;
-  if ((rc = enqueue_eval(ctx, n, d_theta, d_seg, d_fitness, d_argmax, s))) return rc;
+  // The points' descriptors are kept apart from those of the trials.
+  EvalBufs points = own_bufs(ctx), b = own_bufs(ctx);
+  points.evals = ctx->d_pol_evals;
+  if ((rc = enqueue_eval(ctx, points, n, d_theta, d_seg, d_fitness, d_argmax, s))) return rc;
+  const int m = n * n_trials;
   for (int step = 0; step < n_steps; ++step) {
-    // descriptors of the current points (their maximising samples are already in d_argmax)
-    if (step > 0 && (rc = enqueue_setup(ctx, own_bufs(ctx), n, d_theta, d_seg, s, false))) return rc;
-    if ((e = launch_gradient(ctx->prec, ctx->grad, ctx->d_net, ctx->d_segs, ctx->d_evals, d_theta, d_argmax, n,
-                             ctx->net.n_det, ctx->d_pol_grad, s)) !=
+    if ((e = launch_adjoint(ctx->prec, ctx->grad, ctx->d_segs, points.evals, d_argmax, n, ctx->net.n_det, s)) !=
             hipSuccess ||
-        (e = launch_polish_trials(d_theta, ctx->d_pol_grad, d_seg, ctx->d_net, n, n_trials, step_frac,
-                                  ctx->d_pol_cand, ctx->d_pol_seg, s)) != hipSuccess)
+        (e = launch_polish_trials(ctx->grad, ctx->d_net, ctx->d_segs, points.evals, d_theta, d_seg, n, ctx->net.n_det,
+                                  n_trials, step_frac, ctx->d_pol_cand, b.evals, b.lists, b.counts, b.list_stride,
+                                  ctx->d_err, s)) != hipSuccess)
       return hip_fail(e, "polish launch");
-    const int m = n * n_trials;
-    // the trial batch reuses the evaluation buffers: its outputs go to the polish scratch arrays
-    double* cand_f = ctx->d_pol_f;
-    int32_t* cand_j = ctx->d_pol_j;
-    if ((rc = enqueue_eval(ctx, m, ctx->d_pol_cand, ctx->d_pol_seg, cand_f, cand_j, s))) return rc;
-    if ((e = launch_polish_select(d_theta, d_fitness, d_argmax, ctx->d_pol_cand, cand_f, cand_j, n, n_trials, s)) !=
-        hipSuccess)
+    if ((rc = enqueue_passes(ctx, b, m, nullptr, nullptr, s, true, true, false))) {
+      launch_zero_i32(b.counts, kNumPlans, s);
+      return rc;
+    }
+    if ((e = launch_polish_select(ctx->prec, ctx->d_net, ctx->d_segs, points.evals, d_theta, d_seg, d_fitness,
+                                  d_argmax, ctx->d_pol_cand, b.evals, b.part_g, b.part_j, ctx->part_stride,
+                                  ctx->d_plan_parts2, n, n_trials, b.counts, ctx->d_evaluated,
+                                  step + 1 < n_steps ? 1 : 0, ctx->d_err, s)) != hipSuccess) {
+      launch_zero_i32(b.counts, kNumPlans, s);
       return hip_fail(e, "polish select launch");
+    }
   }
   return FCAS_OK;
 }

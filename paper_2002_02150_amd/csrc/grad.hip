@@ -8,6 +8,8 @@
 // the second term being z^H dP z for the derivative of an orthogonal projector.
 #include "grad_kernels.hpp"
 
+#include "setup_kernels.hpp"
+
 namespace fcas {
 
 // Sums NV doubles per lane over the 64 lanes of a wavefront: while the count
@@ -166,18 +168,14 @@ __device__ void coef_derivatives(double tau0, double tau15, double fs, double dc
 // holding detector i for parameter q (alpha, delta, tau0, tau1.5); sums over
 // detectors are butterflies inside a group of 8 lanes.  Bound by the latency
 // of its dependent FP64 operations (8 points: 14 us when one thread did it).
-__global__ void __launch_bounds__(64) k_chain(const NetDesc* __restrict__ netp, const SegDesc* __restrict__ segs,
-                                              const EvalDesc* __restrict__ evals, const double* __restrict__ theta,
-                                              const double* __restrict__ sums, int parts, int n,
-                                              double* __restrict__ grad) {
-  const int e = blockIdx.x, lane = threadIdx.x;
-  const NetDesc& net = *netp;
+// Returns component q in the lanes of group q (0 for a point not evaluated);
+// S: LDS of kMaxDet kAdjSums 2 doubles.
+__device__ __forceinline__ double chain_rule(const NetDesc& net, const SegDesc* __restrict__ segs,
+                                             const EvalDesc* __restrict__ evals, const double* __restrict__ theta,
+                                             const double* __restrict__ sums, int parts, int e, double* S) {
+  const int lane = threadIdx.x;
   const EvalDesc& ev = evals[e];
-  double* g = grad + 4 * (int64_t)e;
-  if (ev.status != 1) {
-    if (lane < 4) g[lane] = 0.0;
-    return;
-  }
+  if (ev.status != 1) return 0.0;
   const int D = net.n_det;
   const int q = (lane >> 3) & 3, i = lane & 7;   // lanes 32..63 repeat lanes 0..31
   const bool on = i < D;
@@ -195,7 +193,6 @@ __global__ void __launch_bounds__(64) k_chain(const NetDesc* __restrict__ netp, 
       pos[a] = net.pos[i][a];
       for (int b = 0; b < 3; ++b) ten[a][b] = net.ten[i][a][b];
     }
-  __shared__ double S[kMaxDet * kAdjSums * 2];
   for (int m = lane; m < D * kAdjSums * 2; m += 64) {
     const int d = m / (kAdjSums * 2), c = m - d * (kAdjSums * 2);
     const double* s = sums + ((int64_t)e * D + d) * parts * kAdjSums * 2 + c;
@@ -234,12 +231,6 @@ __global__ void __launch_bounds__(64) k_chain(const NetDesc* __restrict__ netp, 
   __syncthreads();   // S
   double Si[kAdjSums * 2];
   for (int c = 0; c < kAdjSums * 2; ++c) Si[c] = on ? S[i * kAdjSums * 2 + c] : 0.0;
-  auto sum8 = [](double x) {
-    x += __shfl_xor(x, 1, 8);
-    x += __shfl_xor(x, 2, 8);
-    x += __shfl_xor(x, 4, 8);
-    return x;
-  };
   const double zr = Si[0], zi = Si[1];
   // P z = Q (Q^T z)
   const double c0r = sum8(q0 * zr), c0i = sum8(q0 * zi), c1r = sum8(q1 * zr), c1i = sum8(q1 * zi);
@@ -278,70 +269,154 @@ __global__ void __launch_bounds__(64) k_chain(const NetDesc* __restrict__ netp, 
     const double ti = dV0 * wi0 + dV1 * wi1;
     acc += 2.0 * (rr * tr + ri * ti);
   }
-  acc = sum8(acc);
-  if (lane < 32 && i == 0) g[q] = acc;
+  return sum8(acc);
 }
 
-// Polish trials: theta_t = theta + step_frac 2^-t w^2 g / |w g|, t = 0..T-1
-// (w = widths of the search rectangle), same segment as the point.
-__global__ void k_polish_trials(const double* __restrict__ theta, const double* __restrict__ grad,
-                                const int32_t* __restrict__ seg, const NetDesc* __restrict__ netp, int n, int trials,
-                                double step_frac, double* __restrict__ cand, int32_t* __restrict__ cand_seg) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
+__global__ void __launch_bounds__(64) k_chain(const NetDesc* __restrict__ netp, const SegDesc* __restrict__ segs,
+                                              const EvalDesc* __restrict__ evals, const double* __restrict__ theta,
+                                              const double* __restrict__ sums, int parts, int n,
+                                              double* __restrict__ grad) {
+  __shared__ double S[kMaxDet * kAdjSums * 2];
+  const int e = blockIdx.x, lane = threadIdx.x;
+  const double g = chain_rule(*netp, segs, evals, theta, sums, parts, e, S);
+  if (lane < 32 && (lane & 7) == 0) grad[4 * (int64_t)e + (lane >> 3)] = g;
+}
+
+
+// One polish step around its fitness batch, two kernels of one wavefront per
+// point (bound by latency: as five kernels a step of 8 points took 23 us more).
+//
+// Before it: the gradient by the chain rule, the trials
+//   theta_t = theta + step_frac 2^-t w^2 g / |w g|, t = 0..T-1
+// (w = widths of the search rectangle, same segment as the point) and their
+// set-up, eight at a time.  `evals` holds the points' descriptors, apart from the
+// trials' (`trial_evals`), which other work-groups write meanwhile.
+__global__ void __launch_bounds__(64) k_polish_trials(const NetDesc* __restrict__ netp,
+                                                      const SegDesc* __restrict__ segs,
+                                                      const EvalDesc* __restrict__ evals,
+                                                      const double* __restrict__ theta,
+                                                      const int32_t* __restrict__ seg,
+                                                      const double* __restrict__ sums, int parts, int trials,
+                                                      double step_frac, double* __restrict__ cand,
+                                                      EvalDesc* __restrict__ trial_evals, int32_t* __restrict__ lists,
+                                                      int32_t* __restrict__ counts, int list_stride,
+                                                      int32_t* __restrict__ err) {
+  __shared__ double S[kMaxDet * kAdjSums * 2], th_s[8][4];
   const NetDesc& net = *netp;
-  double w[4], nrm = 0.0;
-  for (int d = 0; d < 4; ++d) {
-    w[d] = net.box_hi[d] - net.box_lo[d];
-    nrm += (w[d] * grad[4 * e + d]) * (w[d] * grad[4 * e + d]);
+  const int e = blockIdx.x, lane = threadIdx.x, k = lane >> 3, d = lane & 3;
+  const SetupSeg q = setup_seg_load(net, segs, seg, e, true);
+  const double gq = chain_rule(net, segs, evals, theta, sums, parts, e, S);
+  double g[4], w[4], nrm = 0.0;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    g[c] = __shfl(gq, 8 * c, 64);
+    w[c] = net.box_hi[c] - net.box_lo[c];
+    nrm += (w[c] * g[c]) * (w[c] * g[c]);
   }
   nrm = sqrt(nrm);
-  double s = step_frac;
-  for (int t = 0; t < trials; ++t) {
+  const double gd = d == 0 ? g[0] : d == 1 ? g[1] : d == 2 ? g[2] : g[3];
+  const double wd = d == 0 ? w[0] : d == 1 ? w[1] : d == 2 ? w[2] : w[3];
+  const double td = theta[4 * (int64_t)e + d];
+  for (int t0 = 0; t0 < trials; t0 += 8) {
+    const int t = t0 + k;
+    const double s = ldexp(step_frac, -t);
+    const double x = td + (nrm > 0.0 ? s * wd * wd * gd / nrm : 0.0);
     const int64_t o = (int64_t)e * trials + t;
-    for (int d = 0; d < 4; ++d)
-      cand[4 * o + d] = theta[4 * e + d] + (nrm > 0.0 ? s * w[d] * w[d] * grad[4 * e + d] / nrm : 0.0);
-    cand_seg[o] = seg[e];
-    s *= 0.5;
+    if ((lane & 7) < 4) {
+      th_s[k][d] = x;
+      if (t < trials) cand[4 * o + d] = x;
+    }
+    __syncthreads();
+    setup_group(net, q, th_s[k], (int)o, t < trials, trial_evals, lists, counts, list_stride, 1, err);
+    __syncthreads();
   }
 }
 
-// Moves each point to its best trial if that raises the fitness.
-__global__ void k_polish_select(double* __restrict__ theta, double* __restrict__ fitness,
-                                int32_t* __restrict__ argmax, const double* __restrict__ cand,
-                                const double* __restrict__ cand_f, const int32_t* __restrict__ cand_j, int n,
-                                int trials) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  int best = -1;
-  double fb = fitness[e];
-  for (int t = 0; t < trials; ++t) {
-    const double f = cand_f[(int64_t)e * trials + t];
-    if (f > fb) {
-      fb = f;
-      best = t;
+// After it: the trials' fitness from their pass-2 partials, each point moved to
+// its best trial if that raises its fitness, and (more) the descriptors of the
+// points for the next step; the work-list counts are cleared.
+template <typename Real>
+__global__ void __launch_bounds__(64) k_polish_select(const NetDesc* __restrict__ netp,
+                                                      const SegDesc* __restrict__ segs, EvalDesc* __restrict__ evals,
+                                                      double* __restrict__ theta, const int32_t* __restrict__ seg,
+                                                      double* __restrict__ fitness, int32_t* __restrict__ argmax,
+                                                      const double* __restrict__ cand,
+                                                      const EvalDesc* __restrict__ trial_evals,
+                                                      const Real* __restrict__ part_g,
+                                                      const int32_t* __restrict__ part_j, int part_stride,
+                                                      const int32_t* __restrict__ plan_parts2, int trials,
+                                                      int32_t* __restrict__ counts,
+                                                      unsigned long long* __restrict__ evaluated, int more,
+                                                      int32_t* __restrict__ err) {
+  __shared__ double f_s[kMaxTrials], th_s[4];
+  __shared__ int32_t j_s[kMaxTrials];
+  const NetDesc& net = *netp;
+  const int e = blockIdx.x, lane = threadIdx.x, k = lane >> 3;
+  const int64_t first = (int64_t)e * trials;
+  const SetupSeg q = setup_seg_load(net, segs, seg, e, more && k == 0);
+  if (e == 0 && lane < kNumPlans) {
+    const int c = counts[lane];
+    counts[lane] = 0;
+    if (c) atomicAdd(evaluated, (unsigned long long)c);
+  }
+  for (int t0 = 0; t0 < trials; t0 += 8) {
+    const int t = t0 + k;
+    if (t < trials) {
+      double f;
+      int j;
+      finalize_value<Real, 8>(trial_evals[first + t], part_g, part_j, part_stride, plan_parts2, (int)(first + t),
+                              lane & 7, f, j);
+      if ((lane & 7) == 0) {
+        f_s[t] = f;
+        j_s[t] = j;
+      }
     }
   }
-  if (best >= 0) {
-    const int64_t o = (int64_t)e * trials + best;
-    for (int d = 0; d < 4; ++d) theta[4 * e + d] = cand[4 * o + d];
-    fitness[e] = fb;
-    argmax[e] = cand_j[o];
+  __syncthreads();
+  int best = -1;
+  double fb = fitness[e];
+  for (int t = 0; t < trials; ++t)
+    if (f_s[t] > fb) {
+      fb = f_s[t];
+      best = t;
+    }
+  if (lane < 4) {
+    const double x = best >= 0 ? cand[4 * (first + best) + lane] : theta[4 * (int64_t)e + lane];
+    th_s[lane] = x;
+    if (best >= 0) theta[4 * (int64_t)e + lane] = x;
   }
+  if (best >= 0 && lane == 0) {
+    fitness[e] = fb;
+    argmax[e] = j_s[best];
+  }
+  if (!more) return;
+  __syncthreads();
+  setup_group(net, q, th_s, e, k == 0, evals, nullptr, nullptr, 0, 0, err);
 }
 
-hipError_t launch_polish_trials(const double* theta, const double* grad, const int32_t* seg, const NetDesc* net,
-                                int n, int trials, double step_frac, double* cand, int32_t* cand_seg,
-                                hipStream_t s) {
-  hipLaunchKernelGGL(k_polish_trials, dim3((n + 63) / 64), dim3(64), 0, s, theta, grad, seg, net, n, trials,
-                     step_frac, cand, cand_seg);
+hipError_t launch_polish_trials(const GradBuffers& g, const NetDesc* net, const SegDesc* segs, const EvalDesc* evals,
+                                const double* theta, const int32_t* seg, int n, int n_det, int trials,
+                                double step_frac, double* cand, EvalDesc* trial_evals, int32_t* lists,
+                                int32_t* counts, int list_stride, int32_t* err, hipStream_t s) {
+  hipLaunchKernelGGL(k_polish_trials, dim3(n), dim3(64), 0, s, net, segs, evals, theta, seg, g.sums,
+                     grad_parts(n, n_det), trials, step_frac, cand, trial_evals, lists, counts, list_stride, err);
   return hipGetLastError();
 }
 
-hipError_t launch_polish_select(double* theta, double* fitness, int32_t* argmax, const double* cand,
-                                const double* cand_f, const int32_t* cand_j, int n, int trials, hipStream_t s) {
-  hipLaunchKernelGGL(k_polish_select, dim3((n + 63) / 64), dim3(64), 0, s, theta, fitness, argmax, cand, cand_f,
-                     cand_j, n, trials);
+hipError_t launch_polish_select(int precision, const NetDesc* net, const SegDesc* segs, EvalDesc* evals,
+                                double* theta, const int32_t* seg, double* fitness, int32_t* argmax,
+                                const double* cand, const EvalDesc* trial_evals, const void* part_g,
+                                const int32_t* part_j, int part_stride, const int32_t* plan_parts2, int n, int trials,
+                                int32_t* counts, unsigned long long* evaluated, int more, int32_t* err,
+                                hipStream_t s) {
+  if (precision == 0)
+    hipLaunchKernelGGL(k_polish_select<float>, dim3(n), dim3(64), 0, s, net, segs, evals, theta, seg, fitness, argmax,
+                       cand, trial_evals, (const float*)part_g, part_j, part_stride, plan_parts2, trials, counts,
+                       evaluated, more, err);
+  else
+    hipLaunchKernelGGL(k_polish_select<double>, dim3(n), dim3(64), 0, s, net, segs, evals, theta, seg, fitness, argmax,
+                       cand, trial_evals, (const double*)part_g, part_j, part_stride, plan_parts2, trials, counts,
+                       evaluated, more, err);
   return hipGetLastError();
 }
 
@@ -374,9 +449,8 @@ void free_grad_buffers(GradBuffers& g) {
   g.sums = nullptr;
 }
 
-hipError_t launch_gradient(int precision, const GradBuffers& g, const NetDesc* net, const SegDesc* segs,
-                           const EvalDesc* evals, const double* theta, const int32_t* argmax, int n, int n_det,
-                           double* grad, hipStream_t s) {
+hipError_t launch_adjoint(int precision, const GradBuffers& g, const SegDesc* segs, const EvalDesc* evals,
+                          const int32_t* argmax, int n, int n_det, hipStream_t s) {
   const int parts = grad_parts(n, n_det);
   const int dt = adj_group(n_det);
   const dim3 grid(n, (n_det + dt - 1) / dt, parts), block(kAdjThreads);
@@ -398,8 +472,15 @@ hipError_t launch_gradient(int precision, const GradBuffers& g, const NetDesc* n
       return hipErrorInvalidValue;
   }
 #undef FCAS_ADJOINT
-  hipError_t e = hipGetLastError();
+  return hipGetLastError();
+}
+
+hipError_t launch_gradient(int precision, const GradBuffers& g, const NetDesc* net, const SegDesc* segs,
+                           const EvalDesc* evals, const double* theta, const int32_t* argmax, int n, int n_det,
+                           double* grad, hipStream_t s) {
+  const hipError_t e = launch_adjoint(precision, g, segs, evals, argmax, n, n_det, s);
   if (e != hipSuccess) return e;
+  const int parts = grad_parts(n, n_det);
   hipLaunchKernelGGL(k_chain, dim3(n), dim3(64), 0, s, net, segs, evals, theta, g.sums, parts, n, grad);
   return hipGetLastError();
 }

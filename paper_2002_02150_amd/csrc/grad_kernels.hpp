@@ -14,6 +14,8 @@ constexpr int kAdjThreads = 256;      // threads of an adjoint block
 constexpr int kAdjMinBlocks = 1024;   // adjoint blocks wanted for small batches
 constexpr int kAdjMaxParts = 64;      // most parts one (point, detector) sum is split into
 
+constexpr int kMaxTrials = 32;        // trials of a polish step
+
 struct GradBuffers {
   double* sums = nullptr;   // [n][n_det][parts][kAdjSums][2]
   int max_batch = 0;
@@ -27,9 +29,18 @@ hipError_t launch_gradient(int precision, const GradBuffers& g, const NetDesc* n
                            const EvalDesc* evals, const double* theta, const int32_t* argmax, int n, int n_det,
                            double* grad, hipStream_t s);
 
-hipError_t launch_polish_trials(const double* theta, const double* grad, const int32_t* seg, const NetDesc* net,
-                                int n, int trials, double step_frac, double* cand, int32_t* cand_seg, hipStream_t s);
-hipError_t launch_polish_select(double* theta, double* fitness, int32_t* argmax, const double* cand,
-                                const double* cand_f, const int32_t* cand_j, int n, int trials, hipStream_t s);
+// The adjoint sums alone, and the two kernels of a polish step (grad.hip).
+hipError_t launch_adjoint(int precision, const GradBuffers& g, const SegDesc* segs, const EvalDesc* evals,
+                          const int32_t* argmax, int n, int n_det, hipStream_t s);
+hipError_t launch_polish_trials(const GradBuffers& g, const NetDesc* net, const SegDesc* segs, const EvalDesc* evals,
+                                const double* theta, const int32_t* seg, int n, int n_det, int trials,
+                                double step_frac, double* cand, EvalDesc* trial_evals, int32_t* lists,
+                                int32_t* counts, int list_stride, int32_t* err, hipStream_t s);
+hipError_t launch_polish_select(int precision, const NetDesc* net, const SegDesc* segs, EvalDesc* evals,
+                                double* theta, const int32_t* seg, double* fitness, int32_t* argmax,
+                                const double* cand, const EvalDesc* trial_evals, const void* part_g,
+                                const int32_t* part_j, int part_stride, const int32_t* plan_parts2, int n, int trials,
+                                int32_t* counts, unsigned long long* evaluated, int more, int32_t* err,
+                                hipStream_t s);
 
 }  // namespace fcas
