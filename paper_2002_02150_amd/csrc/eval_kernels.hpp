@@ -45,7 +45,7 @@ struct PassTune {
 struct PassArgs {
   const SegDesc* segs;
   const EvalDesc* evals;
-  const int32_t* list;     // evaluation indices of this plan, in list order
+  const int32_t* list;     // evaluation indices of this plan, in list order (null: a direct call, see DirectArgs)
   const int32_t* count;    // number of entries in `list`
   void* ws;                // workspace: cap slots of 2 N complex
   void* part_g;            // [max_batch][part_stride] partial maxima (Real)
@@ -57,10 +57,24 @@ struct PassArgs {
   int32_t cap;             // workspace slots (positions per launch)
 };
 
+// What a direct call adds to pass 1 (k_pass1_direct): the points themselves.
+// Such a call has one plan, one launch and no work lists; pass 2 takes point e
+// at position e and passes over those not evaluated.
+struct DirectArgs {
+  const NetDesc* net;
+  const double* theta;
+  const int32_t* seg_ids;
+  EvalDesc* evals;
+  int32_t* err;
+  unsigned long long* evaluated;
+  int32_t plan;            // the launch's plan: a segment of another one is refused
+};
+
 // Number of list positions one launch handles: the chunk [chunk_begin,
 // chunk_begin + cap) of the plan's list, cut to the count the set-up kernel
 // wrote.
 __device__ __forceinline__ int launch_span(const PassArgs& a) {
+  if (!a.list) return a.cap;   // a direct call: every point, in order
   const int cnt = *a.count - a.chunk_begin;
   return cnt < 0 ? 0 : (cnt > a.cap ? a.cap : cnt);
 }
@@ -213,7 +227,9 @@ __device__ __forceinline__ void tile_of_block(int block, int nblocks, int& tile,
 
 // Point (evaluation index) at list position `pos` of the launch, and its
 // segment's descriptor: uniform across the work-group, read as scalar loads.
-__device__ __forceinline__ int list_entry(const PassArgs& a, int pos) { return *const_view(a.list + pos); }
+__device__ __forceinline__ int list_entry(const PassArgs& a, int pos) {
+  return a.list ? *const_view(a.list + pos) : pos;
+}
 
 __device__ __forceinline__ SegDesc segment_of(const PassArgs& a, int e) {
   const int seg = const_view(a.evals + e)->seg;
@@ -497,6 +513,7 @@ __device__ __forceinline__ void pass2_body(const PassArgs& a, cplx<Real>* lds, R
   geo.init(p, tile * PL::RW + r, PL::THREE ? 1 : PL::N1);
   for (; slot < span; slot += step) {
     const int e = list_entry(a, a.chunk_begin + slot);
+    if (!a.list && const_view(a.evals + e)->status != 1) continue;
     cplx<Real> v[2][PL::E2];
     pass2_fetch<Real, PL>(v, (const cplx<Real>*)a.ws + (int64_t)slot * 2 * PL::N, tile, r, p);
     const SegDesc sg = segment_of(a, e);

@@ -478,18 +478,16 @@ int fcas_set_segment_range(fcas_ctx* ctx, int32_t seg_id, int64_t j_lo, int64_t 
 
 namespace {
 
-hipError_t timed_launch(fcas_ctx* ctx, std::vector<TimedPair>& rec, hipStream_t s, int pass, int plan,
-                        const PassArgs& a, int grid) {
-  // with timing on, the launch itself records the two events at the kernel's
-  // start and end (hipExtLaunchKernel)
+// launch(e0, e1) with two timing events (null when timing is off), which the
+// launch itself records at the kernel's start and end (hipExtLaunchKernel).
+template <class Launch>
+hipError_t timed_launch(fcas_ctx* ctx, std::vector<TimedPair>& rec, const Launch& launch) {
   TimedPair tp{};
   if (ctx->timing) {
     hipEventCreate(&tp.a);
     hipEventCreate(&tp.b);
   }
-  hipError_t e = pass == 1   ? launch_pass1(ctx->prec, plan, a, grid, s, tp.a, tp.b)
-                 : pass == 3 ? launch_passm(ctx->prec, plan, a, grid, s, tp.a, tp.b)
-                             : launch_pass2(ctx->prec, plan, a, grid, s, tp.a, tp.b);
+  const hipError_t e = launch(tp.a, tp.b);
   if (ctx->timing) rec.push_back(tp);
   return e;
 }
@@ -589,9 +587,64 @@ int enqueue_fused(fcas_ctx* ctx, const EvalBufs& b, int plan, int n, int cap, hi
 int enqueue_passes(fcas_ctx* ctx, const EvalBufs& b, int32_t n, double* d_fitness, int32_t* d_argmax,
                    hipStream_t s, bool fused_ok, bool timed, bool finalize = true);
 
+// Points of a batch of n that one launch of `plan` takes: as many as the
+// workspace has slots.
+int points_per_launch(const fcas_ctx* ctx, const EvalBufs& b, int plan, int n) {
+  const size_t slot_bytes = 2 * (size_t)kPlans[plan].n * ctx->elt;
+  return std::max(1, (int)std::min<size_t>(b.ws_bytes / slot_bytes, (size_t)n));
+}
+
+// The plan of a call whose pass 1 does the set-up itself (k_pass1_direct), or -1:
+// one two-pass plan in use, the whole call in one launch, and no more pass-1
+// work items than kDirectItems, about what the device holds at once: with a
+// second point to each work-group, setting points up once in a kernel of its
+// own is the shorter way.
+constexpr int kDirectItems = 1024;
+
+int direct_plan(const fcas_ctx* ctx, const EvalBufs& b, int n, bool fused_ok) {
+  if (fused_ok && ctx->schedule == FCAS_SCHEDULE_FUSED) return -1;
+  int only = -1;
+  for (int plan = 0; plan < kNumPlans; ++plan)
+    if (ctx->plan_refs[plan] > 0) {
+      if (only >= 0) return -1;
+      only = plan;
+    }
+  if (only < 0 || kPlans[only].nm > 1 || points_per_launch(ctx, b, only, n) < n) return -1;
+  return (int64_t)n * kPlans[only].tiles1[ctx->prec] <= kDirectItems ? only : -1;
+}
+
+// The passes of a direct call, and finalize.
+int enqueue_direct(fcas_ctx* ctx, const EvalBufs& b, int plan, int32_t n, const double* d_theta, const int32_t* d_seg,
+                   double* d_fitness, int32_t* d_argmax, hipStream_t s, bool timed) {
+  PassArgs a = pass_args(ctx, b, plan, n);
+  a.list = nullptr;
+  const DirectArgs d{ctx->d_net, d_theta, d_seg, b.evals, ctx->d_err, ctx->d_evaluated, plan};
+  const bool was_timing = ctx->timing;
+  ctx->timing = was_timing && timed;
+  hipError_t e = timed_launch(ctx, ctx->t_pass1, [&](hipEvent_t e0, hipEvent_t e1) {
+    return launch_direct(ctx->prec, plan, a, d, n, s, e0, e1);
+  });
+  const char* what = e != hipSuccess ? "direct pass-1 launch" : nullptr;
+  if (!what) {
+    const int g2 = tile_grid(kPlans[plan].tiles2[ctx->prec], n, ctx->grid2[plan]);
+    e = timed_launch(ctx, ctx->t_pass2, [&](hipEvent_t e0, hipEvent_t e1) {
+      return launch_pass2(ctx->prec, plan, a, g2, s, e0, e1);
+    });
+    if (e != hipSuccess) what = "pass-2 launch";
+  }
+  ctx->timing = was_timing;
+  if (what) return hip_fail(e, what);
+  if ((e = launch_finalize(ctx->prec, b.evals, b.part_g, b.part_j, n, ctx->part_stride, ctx->d_plan_parts2, b.counts,
+                           ctx->d_evaluated, d_fitness, d_argmax, s)) != hipSuccess)
+    return hip_fail(e, "finalize launch");
+  return FCAS_OK;
+}
+
 // Enqueues set-up, the FFT passes of every plan in use, and finalize.
 int enqueue_eval(fcas_ctx* ctx, const EvalBufs& b, int32_t n, const double* d_theta, const int32_t* d_seg,
                  double* d_fitness, int32_t* d_argmax, hipStream_t s, bool fused_ok = true, bool timed = true) {
+  const int direct = direct_plan(ctx, b, n, fused_ok);
+  if (direct >= 0) return enqueue_direct(ctx, b, direct, n, d_theta, d_seg, d_fitness, d_argmax, s, timed);
   int rc = enqueue_setup(ctx, b, n, d_theta, d_seg, s);
   if (rc) return rc;
   if ((rc = enqueue_passes(ctx, b, n, d_fitness, d_argmax, s, fused_ok, timed))) {
@@ -625,8 +678,7 @@ int enqueue_passes(fcas_ctx* ctx, const EvalBufs& b, int32_t n, double* d_fitnes
     if (ctx->plan_refs[plan] <= 0) continue;
     const PlanInfo& pi = kPlans[plan];
     const size_t slot_bytes = 2 * (size_t)pi.n * ctx->elt;
-    int cap = (int)std::min<size_t>(b.ws_bytes / slot_bytes, (size_t)n);
-    if (cap < 1) cap = 1;
+    const int cap = points_per_launch(ctx, b, plan, n);
     if (fused && pi.nm == 1 && pi.threads1[0] == pi.threads2[0]) {
       if ((rc = enqueue_fused(ctx, b, plan, n, cap, s))) {
         ctx->timing = was_timing;
@@ -642,12 +694,21 @@ int enqueue_passes(fcas_ctx* ctx, const EvalBufs& b, int32_t n, double* d_fitnes
       const int g1 = tile_grid(pi.tiles1[ctx->prec], m, ctx->grid1[plan]);
       const int g2 = tile_grid(pi.tiles2[ctx->prec], m, ctx->grid2[plan]);
       const char* what = nullptr;
-      if ((e = timed_launch(ctx, ctx->t_pass1, s, 1, plan, a, g1)) != hipSuccess) what = "pass-1 launch";
+      if ((e = timed_launch(ctx, ctx->t_pass1, [&](hipEvent_t e0, hipEvent_t e1) {
+             return launch_pass1(ctx->prec, plan, a, g1, s, e0, e1);
+           })) != hipSuccess)
+        what = "pass-1 launch";
       if (!what && pi.nm > 1) {
         const int gm = std::min(m * pi.tilesm[ctx->prec] * (2 / kPassmSeries), ctx->grid2[plan]);
-        if ((e = timed_launch(ctx, ctx->t_passm, s, 3, plan, a, gm)) != hipSuccess) what = "middle-pass launch";
+        if ((e = timed_launch(ctx, ctx->t_passm, [&](hipEvent_t e0, hipEvent_t e1) {
+               return launch_passm(ctx->prec, plan, a, gm, s, e0, e1);
+             })) != hipSuccess)
+          what = "middle-pass launch";
       }
-      if (!what && (e = timed_launch(ctx, ctx->t_pass2, s, 2, plan, a, g2)) != hipSuccess) what = "pass-2 launch";
+      if (!what && (e = timed_launch(ctx, ctx->t_pass2, [&](hipEvent_t e0, hipEvent_t e1) {
+                      return launch_pass2(ctx->prec, plan, a, g2, s, e0, e1);
+                    })) != hipSuccess)
+        what = "pass-2 launch";
       if (what) {
         ctx->timing = was_timing;
         return hip_fail(e, what);
@@ -855,7 +916,13 @@ namespace fcas {
   template <>                                                                                                      \
   hipError_t launch_pass1_dt<float, DT>(int, const PassArgs&, int, hipStream_t, hipEvent_t, hipEvent_t);           \
   template <>                                                                                                      \
-  hipError_t launch_pass1_dt<double, DT>(int, const PassArgs&, int, hipStream_t, hipEvent_t, hipEvent_t);
+  hipError_t launch_pass1_dt<double, DT>(int, const PassArgs&, int, hipStream_t, hipEvent_t, hipEvent_t);          \
+  template <>                                                                                                      \
+  hipError_t launch_direct_dt<float, DT>(int, const PassArgs&, const DirectArgs&, int, hipStream_t, hipEvent_t,    \
+                                         hipEvent_t);                                                              \
+  template <>                                                                                                      \
+  hipError_t launch_direct_dt<double, DT>(int, const PassArgs&, const DirectArgs&, int, hipStream_t, hipEvent_t,   \
+                                          hipEvent_t);
 FCAS_EACH_DT(FCAS_DECLARE_DT)
 hipError_t launch_passm_f32(int plan, const PassArgs& a, int grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_passm_f64(int plan, const PassArgs& a, int grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
@@ -874,6 +941,18 @@ hipError_t launch_pass1(int precision, int plan, const PassArgs& a, int grid, hi
                      : launch_pass1_dt<float, DT>(plan, a, grid, s, e0, e1);
   switch (a.n_det) {
     FCAS_EACH_DT(FCAS_CASE_DT)
+    default:
+      return hipErrorInvalidValue;
+  }
+}
+hipError_t launch_direct(int precision, int plan, const PassArgs& a, const DirectArgs& d, int n, hipStream_t s,
+                         hipEvent_t e0, hipEvent_t e1) {
+#define FCAS_CASE_DIRECT(DT)                                                       \
+  case DT:                                                                         \
+    return precision ? launch_direct_dt<double, DT>(plan, a, d, n, s, e0, e1)      \
+                     : launch_direct_dt<float, DT>(plan, a, d, n, s, e0, e1);
+  switch (a.n_det) {
+    FCAS_EACH_DT(FCAS_CASE_DIRECT)
     default:
       return hipErrorInvalidValue;
   }

@@ -35,6 +35,13 @@ int fused_blocks_per_cu(int plan);
 template <typename Real, int DT>
 hipError_t launch_pass1_dt(int plan, const PassArgs& a, int grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 
+// pass 1 of a direct call of n points (direct_kernels.hpp), likewise
+template <typename Real, int DT>
+hipError_t launch_direct_dt(int plan, const PassArgs& a, const DirectArgs& d, int n, hipStream_t s, hipEvent_t e0,
+                            hipEvent_t e1);
+hipError_t launch_direct(int precision, int plan, const PassArgs& a, const DirectArgs& d, int n, hipStream_t s,
+                         hipEvent_t e0, hipEvent_t e1);
+
 // precision: 0 float, 1 double; e0 / e1: optional timing events (launch_k)
 hipError_t launch_pass1(int precision, int plan, const PassArgs& a, int grid, hipStream_t s, hipEvent_t e0 = nullptr,
                         hipEvent_t e1 = nullptr);

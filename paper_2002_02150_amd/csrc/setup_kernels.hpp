@@ -63,6 +63,36 @@ __device__ __forceinline__ SetupSeg setup_seg_load(const NetDesc& net, const Seg
   return q;
 }
 
+// Whether a point lies in the search rectangle (finite, bounds included).
+__device__ __forceinline__ bool inside_box(const NetDesc& net, const double* th) {
+  bool inside = true;
+  for (int d = 0; d < 4; ++d) {
+    const double t = th[d];
+    inside = inside && isfinite(t) && t >= net.box_lo[d] && t <= net.box_hi[d];
+  }
+  return inside;
+}
+
+// The FP64 set-up of a point in the rectangle by a group of 8 lanes (lane g):
+// phase coefficients and rank in every lane, detector g in dets.p.
+__device__ __forceinline__ int setup_math(const NetDesc& net, const SetupSeg& q, const double* th, int g,
+                                          double coef[4], DetLanes& dets) {
+  SkyFrame fr;
+  setup_phase(th[2], th[3], net.f_star, coef);
+  // one sine and cosine for both angles: odd lanes take delta's
+  double s1, c1;
+  sincos(th[g & 1], &s1, &c1);
+  const double s2 = dpp_double<0xb1>(s1), c2 = dpp_double<0xb1>(c1);
+  setup_sky(g & 1 ? s2 : s1, g & 1 ? c2 : c1, g & 1 ? s1 : s2, g & 1 ? c1 : c2, fr);
+  dets.on = g < net.n_det;
+  setup_detector(net, q.df, q.sigma_g, fr, dets.on ? g : 0, dets.p);
+  // detector 0's delay ramp, from lane 0 of the group (by its quad, then the
+  // other quad's mirror image)
+  const double d0 = dpp_double<0x00>(dets.p.dly), d1 = dpp_double<0x141>(d0);
+  setup_step(q.dk1, g < 4 ? d0 : d1, dets.p);
+  return setup_basis(dets);
+}
+
 // Set-up of point e (valid) by the 8-lane group holding it, given its segment
 // (setup_seg_load) and its parameters th[4]: status, the FP64 set-up with the
 // per-detector work spread over the lanes, and (build_lists) the append to
@@ -85,28 +115,11 @@ __device__ __forceinline__ void setup_group(const NetDesc& net, const SetupSeg& 
         atomicOr(err, 1);
       }
     } else {
-      bool inside = true;
-      for (int d = 0; d < 4; ++d) {
-        const double t = th[d];
-        inside = inside && isfinite(t) && t >= net.box_lo[d] && t <= net.box_hi[d];
-      }
+      const bool inside = inside_box(net, th);
       if (inside) {
         double coef[4];
-        SkyFrame fr;
-        setup_phase(th[2], th[3], net.f_star, coef);
-        // one sine and cosine for both angles: odd lanes take delta's
-        double s1, c1;
-        sincos(th[g & 1], &s1, &c1);
-        const double s2 = dpp_double<0xb1>(s1), c2 = dpp_double<0xb1>(c1);
-        setup_sky(g & 1 ? s2 : s1, g & 1 ? c2 : c1, g & 1 ? s1 : s2, g & 1 ? c1 : c2, fr);
         DetLanes dets{};
-        dets.on = g < net.n_det;
-        setup_detector(net, q.df, q.sigma_g, fr, dets.on ? g : 0, dets.p);
-        // detector 0's delay ramp, from lane 0 of the group (by its quad, then
-        // the other quad's mirror image)
-        const double d0 = dpp_double<0x00>(dets.p.dly), d1 = dpp_double<0x141>(d0);
-        setup_step(q.dk1, g < 4 ? d0 : d1, dets.p);
-        const int rank = setup_basis(dets);
+        const int rank = setup_math(net, q, th, g, coef, dets);
         if (dets.on) store_detector(ev, g, dets.p);
         if (g == 0) {
           for (int k = 0; k < 4; ++k) ev.coef[k] = coef[k];
