@@ -542,29 +542,46 @@ __global__ void __launch_bounds__(PL::T2)
 // smallest sample, is unique, so any grouping of the reduction gives the same
 // result.
 // ---------------------------------------------------------------------------
+// What is read of a point before its number of partials is known: its status
+// and plan, and the first batch of partials, whether or not it has left that
+// many.
 template <typename Real, int G>
-__device__ __forceinline__ void finalize_value(const EvalDesc& ev, const Real* __restrict__ part_g,
-                                               const int32_t* __restrict__ part_j, int part_stride,
-                                               const int32_t* __restrict__ plan_parts2, int e, int g, double& fitness,
-                                               int& argmax) {
-  constexpr int B = G >= 64 ? 2 : 8;   // loads per lane in flight before any is compared
-  const Real* pg = part_g + (int64_t)e * part_stride;
-  const int32_t* pj = part_j + (int64_t)e * part_stride;
-  // the first batch is read together with the descriptor, whether or not the
-  // point has left that many partials
+struct PointPartials {
+  static constexpr int B = G >= 64 ? 2 : 8;   // loads per lane in flight before any is compared
   Real gv[B];
   int jv[B];
+  int status, plan, count;   // count: partials of a point of that plan
+
+  __device__ __forceinline__ void load(const EvalDesc& ev, const Real* __restrict__ part_g,
+                                       const int32_t* __restrict__ part_j, int part_stride, int e, int g) {
+    const Real* pg = part_g + (int64_t)e * part_stride;
+    const int32_t* pj = part_j + (int64_t)e * part_stride;
 #pragma unroll
-  for (int u = 0; u < B; ++u) {
-    const int t = g + G * u < part_stride ? g + G * u : 0;
-    gv[u] = pg[t];
-    jv[u] = pj[t];
+    for (int u = 0; u < B; ++u) {
+      const int t = g + G * u < part_stride ? g + G * u : 0;
+      gv[u] = pg[t];
+      jv[u] = pj[t];
+    }
+    status = ev.status;
+    plan = ev.plan;
   }
-  const int status = ev.status;
+  __device__ __forceinline__ void load_count(const int32_t* __restrict__ plan_parts2) { count = plan_parts2[plan]; }
+};
+
+template <typename Real, int G>
+__device__ __forceinline__ void finalize_value(PointPartials<Real, G>& pp, const Real* __restrict__ part_g,
+                                               const int32_t* __restrict__ part_j, int part_stride, int e, int g,
+                                               double& fitness, int& argmax) {
+  constexpr int B = PointPartials<Real, G>::B;
+  const Real* pg = part_g + (int64_t)e * part_stride;
+  const int32_t* pj = part_j + (int64_t)e * part_stride;
+  Real(&gv)[B] = pp.gv;
+  int(&jv)[B] = pp.jv;
+  const int status = pp.status;
   Real bg = (Real)-1;
   int bj = 0x7fffffff;
   if (status == 1) {
-    const int nt = plan_parts2[ev.plan];
+    const int nt = pp.count;
     for (int t0 = g;;) {
 #pragma unroll
       for (int u = 0; u < B; ++u)
@@ -603,7 +620,10 @@ __device__ __forceinline__ void finalize_group(const EvalDesc& ev, const Real* _
                                                double* __restrict__ fitness, int32_t* __restrict__ argmax) {
   double f;
   int j;
-  finalize_value<Real, G>(ev, part_g, part_j, part_stride, plan_parts2, e, g, f, j);
+  PointPartials<Real, G> pp;
+  pp.load(ev, part_g, part_j, part_stride, e, g);
+  pp.load_count(plan_parts2);
+  finalize_value<Real, G>(pp, part_g, part_j, part_stride, e, g, f, j);
   if (g == 0) {
     fitness[e] = f;
     argmax[e] = j;

@@ -87,13 +87,35 @@ struct SkyFrame {
   double n[3], ex[3], ey[3];   // propagation direction and wave axes (-alpha_hat, delta_hat)
 };
 
-// Phase coefficients (cycles) of a point.
+// 1 / cbrt(x) and 1 / sqrt(x).
+FCAS_HD double inv_cbrt(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return rcbrt(x);
+#else
+  return 1.0 / std::cbrt(x);
+#endif
+}
+FCAS_HD double inv_sqrt(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return rsqrt(x);
+#else
+  return 1.0 / std::sqrt(x);
+#endif
+}
+
+// Phase coefficients (cycles) of a point.  With x = 5 tau15 / (32 pi tau0),
+// v0 = x^(1/3) and eta = 1 / (8 fs tau15 v0^2),
+//   tau1 = 5 / (192 pi fs eta v0^3) (743/336 + 11/4 eta)
+//   tau2 = 5 / (128 pi fs eta v0) (3058673/1016064 + 5429/1008 eta + 617/144 eta^2),
+// where 1 / (fs eta) = 8 tau15 v0^2: the two quotients that are left do not
+// wait for each other.
 FCAS_HD void setup_phase(double tau0, double tau15, double fs, double coef[4]) {
-  const double v0 = cbrt(5.0 * tau15 / (32.0 * kPi * tau0));
-  const double eta = 1.0 / (8.0 * fs * tau15 * v0 * v0);
-  const double tau1 = 5.0 / (192.0 * kPi * fs * eta * v0 * v0 * v0) * (743.0 / 336.0 + 11.0 * eta / 4.0);
-  const double tau2 = 5.0 / (128.0 * kPi * fs * eta * v0) *
-                      (3058673.0 / 1016064.0 + 5429.0 * eta / 1008.0 + 617.0 * eta * eta / 144.0);
+  const double x = 5.0 * tau15 / (32.0 * kPi * tau0);
+  const double r = inv_cbrt(x), r2 = r * r, v0 = x * r2;
+  const double eta = r2 * (1.0 / (8.0 * fs * tau15));
+  const double tau1 = (40.0 / (192.0 * kPi)) * tau15 * r * (743.0 / 336.0 + 2.75 * eta);
+  const double tau2 = (40.0 / (128.0 * kPi)) * tau15 * v0 *
+                      (3058673.0 / 1016064.0 + eta * (5429.0 / 1008.0 + eta * (617.0 / 144.0)));
   coef[0] = fs * 0.6 * tau0;
   coef[1] = fs * tau1;
   coef[2] = -fs * 1.5 * tau15;
@@ -119,7 +141,7 @@ FCAS_HD void setup_point(const NetDesc& net, const double* th, double coef[4], S
 // the geocentre).
 FCAS_HD double detector_delay(const NetDesc& net, double df, const SkyFrame& fr, int i) {
   const double* r = net.pos[i];
-  return -(fr.n[0] * r[0] + fr.n[1] * r[1] + fr.n[2] * r[2]) / kC * df;
+  return (fr.n[0] * r[0] + fr.n[1] * r[1] + fr.n[2] * r[2]) * (df * (-1.0 / kC));
 }
 
 // What the set-up computes of one detector.
@@ -161,23 +183,25 @@ FCAS_HD int setup_basis(Dets& dets) {
   const double n1 = dets.sum([](const DetPoint& d) { return d.v[1] * d.v[1]; });
   const double vf = n0 + n1;
   const bool second = n1 > n0;   // the larger column
-  const double na = sqrt(second ? n1 : n0);
+  const double na = second ? n1 : n0;
   dets.each([](DetPoint& d) { d.q[0] = d.q[1] = 0.0; });
   int rank = 0;
   if (na > 0.0) {
     rank = 1;
+    const double ia = inv_sqrt(na);
     dets.each([&](DetPoint& d) {
-      d.q[0] = (second ? d.v[1] : d.v[0]) / na;
+      d.q[0] = (second ? d.v[1] : d.v[0]) * ia;
       d.q[1] = second ? d.v[0] : d.v[1];
     });
     for (int pass = 0; pass < 2; ++pass) {
       const double dot = dets.sum([](const DetPoint& d) { return d.q[0] * d.q[1]; });
       dets.each([&](DetPoint& d) { d.q[1] -= dot * d.q[0]; });
     }
-    const double nb = sqrt(dets.sum([](const DetPoint& d) { return d.q[1] * d.q[1]; }));
-    const bool full = nb > 1e-10 * sqrt(vf);
+    const double nb = dets.sum([](const DetPoint& d) { return d.q[1] * d.q[1]; });
+    const bool full = sqrt(nb) > 1e-10 * sqrt(vf);
     if (full) rank = 2;
-    dets.each([&](DetPoint& d) { d.q[1] = full ? d.q[1] / nb : 0.0; });
+    const double ib = full ? inv_sqrt(nb) : 0.0;
+    dets.each([&](DetPoint& d) { d.q[1] *= ib; });
   }
   return rank;
 }

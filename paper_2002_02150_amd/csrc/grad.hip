@@ -364,8 +364,10 @@ __global__ void __launch_bounds__(64) k_polish_select(const NetDesc* __restrict_
     if (t < trials) {
       double f;
       int j;
-      finalize_value<Real, 8>(trial_evals[first + t], part_g, part_j, part_stride, plan_parts2, (int)(first + t),
-                              lane & 7, f, j);
+      PointPartials<Real, 8> pp;
+      pp.load(trial_evals[first + t], part_g, part_j, part_stride, (int)(first + t), lane & 7);
+      pp.load_count(plan_parts2);
+      finalize_value<Real, 8>(pp, part_g, part_j, part_stride, (int)(first + t), lane & 7, f, j);
       if ((lane & 7) == 0) {
         f_s[t] = f;
         j_s[t] = j;

@@ -44,10 +44,50 @@ __global__ void k_pso_init(PsoDev p, double* __restrict__ theta) {
 __global__ void k_pso_step(PsoDev p, const double* __restrict__ fitness, const int32_t* __restrict__ argmax,
                            double* __restrict__ theta) {
   extern __shared__ double sm[];   // PsoShared: pf[P], px[P][4], then pj[P]
-  const int P = p.n_particles;
+  const int P = p.n_particles, r = blockIdx.x, i = threadIdx.x;
   const PsoShared sh{sm, sm + P, (int32_t*)(sm + 5 * P)};
-  PsoLocal L = pso_load(p, blockIdx.x, threadIdx.x);
-  pso_step_run(p, L, fitness, argmax, theta, sh, nullptr, blockIdx.x, threadIdx.x);
+  const int iter = p.iteration[0];
+  const double run_best = p.best_f[r];
+  const int64_t o = (int64_t)r * P + i;
+  double x[4], pbx[4];
+  if (i < P) {
+    const double f = fitness[o];
+    double pb = p.pbest_f[o];
+    int32_t pbj = p.pbest_j[o];
+    const bool better = f > pb;
+    for (int d = 0; d < 4; ++d) {
+      x[d] = p.x[4 * o + d];
+      pbx[d] = better ? x[d] : p.pbest_x[4 * o + d];
+    }
+    if (better) {
+      pb = f;
+      pbj = argmax[o];
+      p.pbest_f[o] = pb;
+      p.pbest_j[o] = pbj;
+      for (int d = 0; d < 4; ++d) p.pbest_x[4 * o + d] = pbx[d];
+    }
+    sh.pf[i] = pb;
+    sh.pj[i] = pbj;
+    for (int d = 0; d < 4; ++d) sh.px[4 * i + d] = pbx[d];
+  }
+  __syncthreads();
+  if (i < 64) pso_run_best(p, sh, run_best, r, i);
+  if (i < P) {
+    const int lb = pso_local_best(sh.pf, i, P);
+    const double w = pso_inertia(p, iter);
+    double r1[4], r2[4];
+    uniforms4(p.seed, (uint32_t)(iter + 1), i, r, 2, r1);
+    uniforms4(p.seed, (uint32_t)(iter + 1), i, r, 3, r2);
+    for (int d = 0; d < 4; ++d) {
+      double vn, xn;
+      pso_move(p, w, r1[d], r2[d], x[d], p.v[4 * o + d], pbx[d], sh.px[4 * lb + d], vn, xn);
+      p.v[4 * o + d] = vn;
+      p.x[4 * o + d] = xn;
+      theta[4 * o + d] = pso_theta(p.lo[d], p.span[d], xn);
+    }
+  }
+  __syncthreads();
+  if (i == 0) pso_advance(p, iter);
 }
 
 // Best of the first u runs of each group of m consecutive runs (one group per

@@ -47,20 +47,40 @@ struct SetupSeg {
   double df, sigma_g;
 };
 
+// The fields of segment q.s.
+__device__ __forceinline__ void setup_seg_fields(SetupSeg& q, int max_segments, int n_det,
+                                                 const SegDesc* __restrict__ segs) {
+  // the descriptor is read ahead of the check; a bad id reads segment 0's
+  const bool in_table = q.s >= 0 && q.s < max_segments;
+  const SegDesc& sg = segs[in_table ? q.s : 0];
+  q.ok = in_table && sg.registered;
+  q.plan = sg.plan;
+  q.dk1 = sg.dk1;
+  q.df = sg.df;
+  const int g = threadIdx.x & 7;
+  q.sigma_g = g < n_det ? sg.sigma[g] : 0.0;
+}
+
 __device__ __forceinline__ SetupSeg setup_seg_load(const NetDesc& net, const SegDesc* __restrict__ segs,
                                                    const int32_t* __restrict__ seg_ids, int e, bool valid) {
   SetupSeg q{};
   if (!valid) return q;
   q.s = seg_ids[e];
-  if (q.s < 0 || q.s >= net.max_segments) return q;
-  const SegDesc& sg = segs[q.s];
-  q.ok = sg.registered;
-  q.plan = sg.plan;
-  q.dk1 = sg.dk1;
-  q.df = sg.df;
-  const int g = threadIdx.x & 7;
-  q.sigma_g = g < net.n_det ? sg.sigma[g] : 0.0;
+  setup_seg_fields(q, net.max_segments, net.n_det, segs);
   return q;
+}
+
+// Sine and cosine of x, reduced to half turns by the product with 1 / pi in two
+// parts (no branch on the size of x: |x| < 2^52).
+__device__ __forceinline__ void sincos_turns(double x, double* s, double* c) {
+  const double i1 = 0x1.45f306dc9c883p-2, i2 = -0x1.6b01ec5417056p-56;   // 1 / pi
+  const double t = x * i1, k = rint(t);
+  const double e = __builtin_fma(x, i2, __builtin_fma(x, i1, -t));
+  double sn, cs;
+  sincospi((t - k) + e, &sn, &cs);
+  const bool odd = k != 2.0 * rint(0.5 * k);
+  *s = odd ? -sn : sn;
+  *c = odd ? -cs : cs;
 }
 
 // Whether a point lies in the search rectangle (finite, bounds included).
@@ -81,7 +101,7 @@ __device__ __forceinline__ int setup_math(const NetDesc& net, const SetupSeg& q,
   setup_phase(th[2], th[3], net.f_star, coef);
   // one sine and cosine for both angles: odd lanes take delta's
   double s1, c1;
-  sincos(th[g & 1], &s1, &c1);
+  sincos_turns(g & 1 ? th[1] : th[0], &s1, &c1);
   const double s2 = dpp_double<0xb1>(s1), c2 = dpp_double<0xb1>(c1);
   setup_sky(g & 1 ? s2 : s1, g & 1 ? c2 : c1, g & 1 ? s1 : s2, g & 1 ? c1 : c2, fr);
   dets.on = g < net.n_det;
