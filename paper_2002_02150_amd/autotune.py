@@ -1,6 +1,7 @@
 """FFT plan autotuner: times every plan of each segment length on this device,
 over a grid of persistent work-group counts for the two passes, and writes the
-fastest choice per length to tuning.json (applied by Context by default).
+fastest choice per length to tuning.json (applied by Context by default), every
+measurement to tuning_measurements.json beside it.
 
     python -m paper_2002_02150_amd.autotune [--lengths 131072,262144] [--out PATH]
 
@@ -112,9 +113,13 @@ def autotune(lengths=DEFAULT_LENGTHS, n_det=4, fs=2048.0, batches=(16, 256), rep
                what="mean device time of one fitness call (set-up, passes, finalize), geometric mean over the batches",
                written=time.strftime("%Y-%m-%d %H:%M:%S"), choices=choices, measurements=results)
     if out:
-        with open(out, "w") as fh:
-            json.dump(doc, fh, indent=1)
-            fh.write("\n")
+        # every context reads `out` when it is created, so it holds the choices
+        # alone; the measurements behind them go beside it
+        for path, part in ((out, {k: v for k, v in doc.items() if k != "measurements"}),
+                           (os.path.splitext(out)[0] + "_measurements.json", doc)):
+            with open(path, "w") as fh:
+                json.dump(part, fh, indent=1)
+                fh.write("\n")
     return doc
 
 
