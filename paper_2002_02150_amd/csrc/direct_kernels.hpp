@@ -21,8 +21,9 @@ __device__ __forceinline__ T uniform_copy(const T& x) {
 // sets the point up (every work-group of the point does, in LDS; tile 0's also
 // writes the descriptor) while the segment data are on their way, so a call
 // that gives no work-group a second point needs no set-up kernel, no work list
-// and no reads of a descriptor that another kernel wrote.  One point of
-// 131072: set-up kernel and pass 1 4.2 + 7.5 us, this one 8.6.
+// and no reads of a descriptor that another kernel wrote.  Bound by latency
+// (the set-up's dependent operations, one round of the tile's transform): one
+// point of 131072 samples, set-up kernel and pass 1 4.2 + 8.2 us, this one 9.2.
 template <typename Real, class PL, int DT>
 __global__ void __launch_bounds__(PL::T1) __attribute__((amdgpu_waves_per_eu(PassTune<Real, PL, DT>::waves1)))
 k_pass1_direct(PassArgs a, DirectArgs d) {

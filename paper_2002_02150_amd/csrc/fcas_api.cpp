@@ -598,7 +598,9 @@ int points_per_launch(const fcas_ctx* ctx, const EvalBufs& b, int plan, int n) {
 // one two-pass plan in use, the whole call in one launch, and no more pass-1
 // work items than kDirectItems, about what the device holds at once: with a
 // second point to each work-group, setting points up once in a kernel of its
-// own is the shorter way.
+// own is the shorter way.  Measured, us per call (set-up kernel -> direct): one
+// point of 131072 samples 18.8 -> 16.6; at 1024 items (128 points of 16384)
+// 32.9 -> 30.8; at 2048 (256 points) 39.3 -> 40.7.
 constexpr int kDirectItems = 1024;
 
 int direct_plan(const fcas_ctx* ctx, const EvalBufs& b, int n, bool fused_ok) {
