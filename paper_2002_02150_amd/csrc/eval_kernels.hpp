@@ -391,7 +391,7 @@ __global__ void __launch_bounds__(PL::TM) k_passm(PassArgs a) {
 
 // ---------------------------------------------------------------------------
 // Pass 2: length-N2 row FFTs, |a_0|^2 + |a_1|^2 and its maximum over the rows
-// of one work item -> one partial (value, sample) per wavefront.  When every
+// of one work item -> one partial (value, sample) per work item.  When every
 // row transform lies inside one wavefront the items need no work-group
 // barrier; rows longer than a wavefront's share synchronise the work-group.
 // ---------------------------------------------------------------------------

@@ -15,8 +15,9 @@
 namespace fcas {
 
 // Pass 2 leaves one partial (maximum, sample) per work item: TILES2 per
-// evaluation, at most kMaxParts2 over all plans.  A context sizes its partial buffers by the largest count among the plans its
-// maximum segment length admits.
+// evaluation, at most kMaxParts2 over all plans.  A context sizes its partial
+// buffers by the largest count among the plans its maximum segment length
+// admits.
 constexpr int kMaxParts2 = 4096;
 
 template <int... R>
