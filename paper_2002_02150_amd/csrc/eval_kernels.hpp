@@ -29,7 +29,9 @@ namespace fcas {
 //   waves: occupancy the kernel is compiled for (waves per SIMD).
 // Float transforms of 8-element threads fit in 128 VGPRs: 4 waves; pass 1 of
 // 12 or 16 elements with its data kept takes 190-210 (320 points of 196608 in
-// 192-point columns: 199 us at 2 waves, 212 at 3 with spills).
+// 192-point columns: 199 us at 2 waves, 212 at 3 with spills).  Double: 3 waves
+// for 8 elements, 2 for more (12 elements spill 97 VGPRs at 3: 40 points of
+// 98304 95 us a call, 71 at 2).
 //   keep: pass 1 holds a tile's segment data in registers from point to point
 //   (where they leave room for the transform), else it reads them again.
 template <typename Real, class PL, int DT = 1>
@@ -38,7 +40,7 @@ struct PassTune {
   static constexpr bool joint1 = f32 && PL::E1 <= 12, joint2 = f32 && PL::E2 <= 12;
   static constexpr int data1 = (DT * 2 * (int)sizeof(Real) / 4 + 2) * (PL::E1 / 2);   // registers of the segment data
   static constexpr bool keep = data1 <= (f32 && PL::E1 > 8 ? 80 : 40);
-  static constexpr int waves1 = FCAS_PASS1_WAVES >= 0 ? FCAS_PASS1_WAVES : !f32 ? 3 : PL::E1 == 8 ? 4 : 2;
+  static constexpr int waves1 = FCAS_PASS1_WAVES >= 0 ? FCAS_PASS1_WAVES : !f32 ? (PL::E1 == 8 ? 3 : 2) : PL::E1 == 8 ? 4 : 2;
   static constexpr int waves2 = FCAS_PASS2_WAVES >= 0 ? FCAS_PASS2_WAVES : (f32 && PL::E2 == 8 ? 4 : 3);
 };
 

@@ -106,6 +106,50 @@ FCAS_HD void sincos_rev(double r, double* s, double* c) {
 #endif
 }
 
+// e^{+2 pi i m / d} in double for whole numbers 0 <= m / d < EIGHTHS / 8, d a
+// multiple of 8 below 2^29.  Reduced in whole numbers to at most an eighth of a
+// turn, by the steps that EIGHTHS (1, 2, 4 or 8) leaves, then the Taylor series
+// of the sine (to t^17, 2 pi in two parts) and cosine (to t^16), which end
+// below 2e-18 there; an error of at most 1.3 units of 2^-53 altogether.
+template <int EIGHTHS>
+FCAS_HD cplx<double> unit_root(int m, int d) {
+  const bool conj = EIGHTHS > 4 && 2 * m > d;
+  if (conj) m = d - m;
+  const bool quarter = EIGHTHS > 2 && 4 * m > d;
+  if (quarter) m -= d / 4;
+  const bool mirror = EIGHTHS > 1 && 8 * m > d;
+  if (mirror) m = d / 4 - m;
+  const double inv = 1.0 / (double)d;
+  double t = (double)m * inv;
+  if (d & (d - 1)) t = __builtin_fma(__builtin_fma(-t, (double)d, (double)m), inv, t);
+  const double u = t * t;
+  // coefficients (2 pi)^n / n! with alternating signs
+  double p = __builtin_fma(u, 0.10422916220813984, -0.7181223017785006);
+  p = __builtin_fma(u, p, 3.819952584848282);
+  p = __builtin_fma(u, p, -15.09464257682299);
+  p = __builtin_fma(u, p, 42.058693944897655);
+  p = __builtin_fma(u, p, -76.70585975306139);
+  p = __builtin_fma(u, p, 81.60524927607506);
+  p = __builtin_fma(u, p, -41.34170224039976);
+  p = __builtin_fma(u, p, 2.4492935982947064e-16);
+  const double sn = __builtin_fma(t, 6.283185307179586, t * p);
+  double q = __builtin_fma(u, 0.28200596845579123, -1.714390711088672);
+  q = __builtin_fma(u, q, 7.903536371318469);
+  q = __builtin_fma(u, q, -26.4262567833744);
+  q = __builtin_fma(u, q, 60.24464137187666);
+  q = __builtin_fma(u, q, -85.45681720669373);
+  q = __builtin_fma(u, q, 64.9393940226683);
+  q = __builtin_fma(u, q, -19.739208802178716);
+  const double cs = __builtin_fma(u, q, 1.0);
+  double x = mirror ? sn : cs, y = mirror ? cs : sn;
+  if (quarter) {
+    const double x0 = x;
+    x = -y;
+    y = x0;
+  }
+  return mk<double>(x, conj ? -y : y);
+}
+
 // e^{+2 pi i m / L} for integer 0 <= m < L
 template <typename R>
 FCAS_HD cplx<R> twiddle(int m, int L) {
@@ -501,6 +545,12 @@ constexpr int geo_off(int R, int f) {
   return 0;
 }
 
+// Bound on its angle in eighths of a turn, s being below a turn / R: 1, 2, 4 or 8.
+constexpr int geo_eighths(int R, int f) {
+  const int x = 16 * geo_mul(R, f) + geo_off(R, f) * R;   // of 2 R
+  return x <= 2 * R ? 1 : x <= 4 * R ? 2 : x <= 8 * R ? 4 : 8;
+}
+
 template <int R, typename T>
 FCAS_HD void dft_geo(cplx<T>* x, const cplx<T>* w) {
   if constexpr (R == 2) {
@@ -533,40 +583,32 @@ FCAS_HD void dft_geo(cplx<T>* x, const cplx<T>* w) {
   }
 }
 
-// The factors of ratio s = exp(2 pi i num / den), num / den < 1 / R.  Float:
-// each from its own hardware sine and cosine (powers of s would multiply
-// their error: 4e-7 of the fitness became 1.6e-6); double: powers of s (error
-// of a few 1e-16).
-template <int R, typename T>
-FCAS_HD void geo_factors(cplx<T>* w, int num, int den) {
-  if constexpr (sizeof(T) == 4) {
-#pragma unroll
-    for (int f = 0; f < geo_count(R); ++f) {
-      if (R == 8 && f == 3) {   // s w8
-        const T h = (T)0.70710678118654752440;
-        w[3] = mk<T>(h * (w[2].x - w[2].y), h * (w[2].x + w[2].y));
-        continue;
-      }
-      T r = (T)(geo_mul(R, f) * num) / (T)den + (T)geo_off(R, f) * (T)0.0625;
+// The factors of ratio s = exp(2 pi i num / den), num / den < 1 / R, each from
+// a sine and cosine of its own: powers of s would multiply its error (float:
+// 4e-7 of the fitness became 1.6e-6; double: s^8 off by up to 8.6 units of 2^-53
+// instead of 1.7, a row of 1024 = 16 8 8 points by 1.2e-15 rms instead of 3.4e-16).
+template <int R, int F, typename T>
+FCAS_HD void geo_factor(cplx<T>* w, int num, int den) {
+  if constexpr (F < geo_count(R)) {
+    if constexpr (sizeof(T) == 8) {
+      // (16 den < 2^29)
+      w[F] = unit_root<geo_eighths(R, F)>(16 * geo_mul(R, F) * num + geo_off(R, F) * den, 16 * den);
+    } else if constexpr (R == 8 && F == 3) {   // s w8
+      const T h = (T)0.70710678118654752440;
+      w[3] = mk<T>(h * (w[2].x - w[2].y), h * (w[2].x + w[2].y));
+    } else {
+      T r = (T)(geo_mul(R, F) * num) / (T)den + (T)geo_off(R, F) * (T)0.0625;
       if (r > (T)0.5) r -= (T)1;
       T sn, cs;
       sincos_rev(r, &sn, &cs);
-      w[f] = mk<T>(cs, sn);
+      w[F] = mk<T>(cs, sn);
     }
-  } else {
-    cplx<T> pw[4];   // s, s^2, s^4, s^8
-    pw[0] = twiddle<T>(num, den);
-#pragma unroll
-    for (int k = 1; k < 4; ++k) pw[k] = mul(pw[k - 1], pw[k - 1]);
-    const T c1 = (T)0.92387953251128675613, s1 = (T)0.38268343236508977173, r2 = (T)0.70710678118654752440;
-    const cplx<T> root[4] = {mk<T>(1, 0), mk<T>(c1, s1), mk<T>(r2, r2), mk<T>(s1, c1)};   // w16^0..3
-#pragma unroll
-    for (int f = 0; f < geo_count(R); ++f) {
-      const int m = geo_mul(R, f), o = geo_off(R, f);
-      const cplx<T> b = pw[m == 1 ? 0 : m == 2 ? 1 : m == 4 ? 2 : 3];
-      w[f] = o ? mul(b, root[o]) : b;
-    }
+    geo_factor<R, F + 1>(w, num, den);
   }
+}
+template <int R, typename T>
+FCAS_HD void geo_factors(cplx<T>* w, int num, int den) {
+  geo_factor<R, 0>(w, num, den);
 }
 
 // ---------------------------------------------------------------------------
