@@ -39,7 +39,7 @@ N_SAMPLES, FS, F_LOW, F_HIGH = 131072, 2048.0, 30.0, 1000.0
 RUNS, PARTICLES = 8, 40
 HBM_PEAK_GBS = 8000.0
 KERNEL_SOURCES = ("fft_core.hpp", "fitness_tiles.hpp", "plans.hpp", "eval_kernels.hpp", "direct_kernels.hpp",
-                  "eval_pass1.hip", "eval_f32.hip", "fcas_api.cpp")
+                  "rules.hpp", "eval_pass1.hip", "eval_f32.hip", "fcas_api.cpp")
 
 
 def parse():

@@ -8,6 +8,7 @@
 
 #include "fitness_tiles.hpp"
 #include "plans.hpp"
+#include "rules.hpp"
 
 // Build-time overrides of the occupancy each pass kernel is compiled for
 // (waves per SIMD; -1: the per-plan choice of PassTune below).
@@ -53,7 +54,7 @@ struct PassArgs {
   void* part_g;            // [max_batch][part_stride] partial maxima (Real)
   int32_t* part_j;         // [max_batch][part_stride] their samples
   int32_t part_stride;     // partials per evaluation slot (>= the plan's PARTS2)
-  int32_t nt;              // non-temporal pass-1 stores
+  int32_t nt;              // pass-1 stores (StorePolicy)
   int32_t n_det;
   int32_t chunk_begin;     // first list position handled by this launch
   int32_t cap;             // workspace slots (positions per launch)
@@ -247,6 +248,15 @@ struct PassLds {
   static constexpr int X2 = (PassTune<Real, PL>::joint2 ? 2 : 1) * PL::RW * LP2;
 };
 
+// Whether a launch of `span` points stores non-temporally.  Points of one
+// segment usually stand together, so its first and last point tell whether it
+// holds several (either policy gives the same results).
+__device__ __forceinline__ bool streams_rows(const PassArgs& a, int span) {
+  if (a.nt != kStoreBySegments) return a.nt == kStoreStreamed;
+  return const_view(a.evals + list_entry(a, a.chunk_begin))->seg !=
+         const_view(a.evals + list_entry(a, a.chunk_begin + span - 1))->seg;
+}
+
 // Pass 1 on the share of work-group `block` of `nblocks`.  The segment data of
 // the tile are read when the segment changes and stay in registers for the
 // points that follow.
@@ -265,6 +275,7 @@ __device__ __forceinline__ void pass1_body(const PassArgs& a, cplx<Real>* lds, i
   Pass1Data<Real, PL, DT> d;
   Pass1Geo<Real, PL> g;
   g.init(p);
+  const bool nt = streams_rows(a, span);
   for (; slot < span; slot += step) {
     const int e = list_entry(a, a.chunk_begin + slot);
     const int seg = const_view(a.evals + e)->seg;
@@ -276,7 +287,7 @@ __device__ __forceinline__ void pass1_body(const PassArgs& a, cplx<Real>* lds, i
     cplx<Real> v[2][PL::E1];
     pass1_compute<Real, PL, DT>(v, d, pass1_point<Real, DT>(const_view(a.evals + e)));
     cplx<Real>* out = (cplx<Real>*)a.ws + (int64_t)slot * 2 * PL::N;
-    if (a.nt)
+    if (nt)
       pass1_transform<Real, PL, true>(v, out, buf0, buf1, g, tile, c, p);
     else
       pass1_transform<Real, PL, false>(v, out, buf0, buf1, g, tile, c, p);

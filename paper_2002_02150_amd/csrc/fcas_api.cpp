@@ -15,6 +15,7 @@
 #include "grad_kernels.hpp"
 #include "launch.hpp"
 #include "pso_kernels.hpp"
+#include "rules.hpp"
 
 using namespace fcas;
 
@@ -26,13 +27,6 @@ namespace {
 // points of 131072 take it 126 us with 1024 work-groups, 106 with 16384 (pass 1
 // 118 with 1024, 150 with 8192).
 constexpr int kDefaultGrid1 = 1024, kDefaultGrid2 = 16384;
-
-// Pass-1 output of a launch beyond which its stores are non-temporal.
-// Measured: 192 points of 131072 (403 MB) 87 us with non-temporal stores, 86
-// through the L2; 2048 points (4.3 GB) 800 and 835; shorter lengths of smaller
-// launches gain more from the L2 (320 points of 65536: 75 and 61; 196608: 202
-// and 183).
-constexpr size_t kNtBytes = (size_t)1 << 30;
 
 thread_local std::string g_last_error;
 
@@ -541,7 +535,7 @@ PassArgs pass_args(fcas_ctx* ctx, const EvalBufs& b, int plan, int cap) {
   a.n_det = ctx->net.n_det;
   a.chunk_begin = 0;
   a.cap = cap;
-  a.nt = 0;
+  a.nt = kStoreCached;
   return a;
 }
 
@@ -692,7 +686,7 @@ int enqueue_passes(fcas_ctx* ctx, const EvalBufs& b, int32_t n, double* d_fitnes
     for (int begin = 0; begin < n; begin += cap) {
       a.chunk_begin = begin;
       const int m = std::min(cap, n - begin);
-      a.nt = m * slot_bytes > kNtBytes ? 1 : 0;
+      a.nt = store_policy(m * slot_bytes);
       const int g1 = tile_grid(pi.tiles1[ctx->prec], m, ctx->grid1[plan]);
       const int g2 = tile_grid(pi.tiles2[ctx->prec], m, ctx->grid2[plan]);
       const char* what = nullptr;

@@ -1,0 +1,33 @@
+"""The choices the library makes from the sizes of a call, at both sides of
+each line, on the CPU."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("rules") / "rules_check")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I" + os.path.join(ROOT, "paper_2002_02150_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "emu", "rules_check.cpp"), "-o", exe], check=True)
+
+    def ask(*args):
+        return int(subprocess.run([exe, *map(str, args)], check=True, capture_output=True, text=True).stdout)
+    return ask
+
+
+def _rows(points, n, fp64=False):
+    return points * 2 * n * (16 if fp64 else 8)
+
+
+@pytest.mark.parametrize("nbytes,policy", [
+    (_rows(109, 131072), 0), ((1 << 28) - 1, 0),      # through the L2: pass 2 finds the rows in the caches
+    (1 << 28, 2), (_rows(320, 131072), 2),            # non-temporal if the launch holds several segments
+    (_rows(190, 262144), 2), (_rows(100, 131072, True), 2), (1 << 30, 2),
+    ((1 << 30) + 1, 1), (_rows(2048, 131072), 1),     # non-temporal
+])
+def test_store_policy(rule, nbytes, policy):
+    assert rule("store", nbytes) == policy
