@@ -589,14 +589,8 @@ int points_per_launch(const fcas_ctx* ctx, const EvalBufs& b, int plan, int n) {
 }
 
 // The plan of a call whose pass 1 does the set-up itself (k_pass1_direct), or -1:
-// one two-pass plan in use, the whole call in one launch, and no more pass-1
-// work items than kDirectItems, about what the device holds at once: with a
-// second point to each work-group, setting points up once in a kernel of its
-// own is the shorter way.  Measured, us per call (set-up kernel -> direct): one
-// point of 131072 samples 18.8 -> 16.6; at 1024 items (128 points of 16384)
-// 32.9 -> 30.8; at 2048 (256 points) 39.3 -> 40.7.
-constexpr int kDirectItems = 1024;
-
+// one two-pass plan in use, the whole call in one launch, and few enough
+// work-groups (direct_call).
 int direct_plan(const fcas_ctx* ctx, const EvalBufs& b, int n, bool fused_ok) {
   if (fused_ok && ctx->schedule == FCAS_SCHEDULE_FUSED) return -1;
   int only = -1;
@@ -606,7 +600,8 @@ int direct_plan(const fcas_ctx* ctx, const EvalBufs& b, int n, bool fused_ok) {
       only = plan;
     }
   if (only < 0 || kPlans[only].nm > 1 || points_per_launch(ctx, b, only, n) < n) return -1;
-  return (int64_t)n * kPlans[only].tiles1[ctx->prec] <= kDirectItems ? only : -1;
+  return direct_call(n, kPlans[only].tiles1[ctx->prec], kPlans[only].threads1[ctx->prec], ctx->prec, ctx->n_cu) ? only
+                                                                                                               : -1;
 }
 
 // The passes of a direct call, and finalize.

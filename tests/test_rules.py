@@ -31,3 +31,17 @@ def _rows(points, n, fp64=False):
 ])
 def test_store_policy(rule, nbytes, policy):
     assert rule("store", nbytes) == policy
+
+
+@pytest.mark.parametrize("points,tiles,threads,fp64,direct", [
+    (1, 32, 256, 0, 1), (32, 32, 256, 0, 1), (33, 32, 256, 0, 0),      # 131072 float: four groups a CU
+    (8, 64, 512, 0, 1), (9, 64, 512, 0, 0),                            # 262144 float: two of 512 threads
+    (2, 128, 1024, 0, 1), (3, 128, 1024, 0, 0),                        # one of 1024 threads
+    (12, 64, 256, 1, 1), (13, 64, 256, 1, 0),                          # 131072 double: three
+    (16, 64, 128, 1, 1), (17, 64, 128, 1, 0),                          # 98304 double: never more than four
+    (384, 1, 256, 0, 1), (385, 1, 256, 0, 0), (384, 1, 256, 1, 1), (385, 1, 256, 1, 0),   # 2048: points
+    (1 << 24, 256, 512, 0, 0),
+])
+def test_direct_calls(rule, points, tiles, threads, fp64, direct):
+    """A call sets its points up in pass 1 while its work-groups start together."""
+    assert rule("direct", points, tiles, threads, fp64, 256) == direct
