@@ -581,6 +581,13 @@ int enqueue_fused(fcas_ctx* ctx, const EvalBufs& b, int plan, int n, int cap, hi
 int enqueue_passes(fcas_ctx* ctx, const EvalBufs& b, int32_t n, double* d_fitness, int32_t* d_argmax,
                    hipStream_t s, bool fused_ok, bool timed, bool finalize = true);
 
+// Whether the context takes points of `plan` through the fused schedule.
+bool runs_fused(const fcas_ctx* ctx, int plan) {
+  const PlanInfo& pi = kPlans[plan];
+  return ctx->schedule == FCAS_SCHEDULE_FUSED && pi.nm == 1 && pi.threads1[0] == pi.threads2[0] &&
+         fused_takes(pi.tiles1[0] + pi.tiles2[0]);
+}
+
 // Points of a batch of n that one launch of `plan` takes: as many as the
 // workspace has slots.
 int points_per_launch(const fcas_ctx* ctx, const EvalBufs& b, int plan, int n) {
@@ -592,7 +599,6 @@ int points_per_launch(const fcas_ctx* ctx, const EvalBufs& b, int plan, int n) {
 // one two-pass plan in use, the whole call in one launch, and few enough
 // work-groups (direct_call).
 int direct_plan(const fcas_ctx* ctx, const EvalBufs& b, int n, bool fused_ok) {
-  if (fused_ok && ctx->schedule == FCAS_SCHEDULE_FUSED) return -1;
   int only = -1;
   for (int plan = 0; plan < kNumPlans; ++plan)
     if (ctx->plan_refs[plan] > 0) {
@@ -600,6 +606,7 @@ int direct_plan(const fcas_ctx* ctx, const EvalBufs& b, int n, bool fused_ok) {
       only = plan;
     }
   if (only < 0 || kPlans[only].nm > 1 || points_per_launch(ctx, b, only, n) < n) return -1;
+  if (fused_ok && runs_fused(ctx, only)) return -1;
   return direct_call(n, kPlans[only].tiles1[ctx->prec], kPlans[only].threads1[ctx->prec], ctx->prec, ctx->n_cu) ? only
                                                                                                                : -1;
 }
@@ -652,16 +659,18 @@ int enqueue_eval(fcas_ctx* ctx, int32_t n, const double* d_theta, const int32_t*
 }
 
 // The FFT passes of every plan in use, then (finalize) the finalize kernel,
-// which clears the work-list counts.  Plans with a middle pass, or with passes
-// of unequal work items, always run as separate launches (the fused schedule
-// covers the other two-pass plans, when fused_ok).  With `timed` false no
+// which clears the work-list counts.  Plans that the context does not take
+// through the fused schedule (runs_fused, and fused_ok) run as separate
+// launches.  With `timed` false no
 // timing events are recorded whatever the context's setting.
 int enqueue_passes(fcas_ctx* ctx, const EvalBufs& b, int32_t n, double* d_fitness, int32_t* d_argmax,
                    hipStream_t s, bool fused_ok, bool timed, bool finalize) {
   hipError_t e;
   int rc;
-  const bool fused = fused_ok && ctx->schedule == FCAS_SCHEDULE_FUSED;
-  if (fused && (e = launch_zero_i32(ctx->d_done, 2 * kNumPlans * ctx->cfg.max_batch, s)) != hipSuccess)
+  bool any_fused = false;
+  for (int plan = 0; plan < kNumPlans; ++plan)
+    any_fused = any_fused || (fused_ok && ctx->plan_refs[plan] > 0 && runs_fused(ctx, plan));
+  if (any_fused && (e = launch_zero_i32(ctx->d_done, 2 * kNumPlans * ctx->cfg.max_batch, s)) != hipSuccess)
     return hip_fail(e, "zero tile counters");
   const bool was_timing = ctx->timing;
   ctx->timing = was_timing && timed;
@@ -670,7 +679,7 @@ int enqueue_passes(fcas_ctx* ctx, const EvalBufs& b, int32_t n, double* d_fitnes
     const PlanInfo& pi = kPlans[plan];
     const size_t slot_bytes = 2 * (size_t)pi.n * ctx->elt;
     const int cap = points_per_launch(ctx, b, plan, n);
-    if (fused && pi.nm == 1 && pi.threads1[0] == pi.threads2[0]) {
+    if (fused_ok && runs_fused(ctx, plan)) {
       if ((rc = enqueue_fused(ctx, b, plan, n, cap, s))) {
         ctx->timing = was_timing;
         return rc;

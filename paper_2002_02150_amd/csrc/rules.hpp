@@ -42,4 +42,12 @@ inline bool direct_call(int points, int tiles, int threads, bool fp64, int n_cu)
   return groups * (threads / 64) <= (fp64 ? 12 : 16) * n_cu && groups <= 4 * n_cu && 2 * points <= 3 * n_cu;
 }
 
+// Whether the fused schedule takes a two-pass plan of so many work items
+// (tiles of both passes) a point in one persistent launch.  Every item signals,
+// and every second one waits, at device scope, so its launch grows with the
+// items: us for 320 points, fused / separate launches: 8192 (8 items) 104 / 34,
+// 16384 (16) 331 / 48, 32768 (32) 1450 / 81, 131072 (96) 1920 / 270.  It is kept
+// where it costs least; longer points run as separate launches, same bits.
+inline bool fused_takes(int items) { return items <= 8; }
+
 }  // namespace fcas

@@ -45,3 +45,9 @@ def test_store_policy(rule, nbytes, policy):
 def test_direct_calls(rule, points, tiles, threads, fp64, direct):
     """A call sets its points up in pass 1 while its work-groups start together."""
     assert rule("direct", points, tiles, threads, fp64, 256) == direct
+
+
+@pytest.mark.parametrize("items,fused", [(2, 1), (8, 1), (9, 0), (16, 0), (96, 0)])
+def test_fused_schedule(rule, items, fused):
+    """The fused schedule takes points of few work items."""
+    assert rule("fused", items) == fused
