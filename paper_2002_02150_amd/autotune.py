@@ -72,13 +72,20 @@ def time_plan(ctx, plan, g1, g2, xf, psd, theta, seg, reps):
     return min(samples)
 
 
-def autotune(lengths=DEFAULT_LENGTHS, n_det=4, fs=2048.0, batches=(16, 256), reps=10, grids1=GRIDS1, grids2=GRIDS2,
-             out=fcas.TUNING_PATH, device=0, log=print):
+def autotune(lengths=DEFAULT_LENGTHS, n_det=4, fs=2048.0, batch=None, reps=10, grids=None, out=fcas.TUNING_PATH,
+             device=0, log=print, batches=(16, 256), grids1=GRIDS1, grids2=GRIDS2):
+    """Times the plans of `lengths` and writes the choices to `out`.  `batch`: one
+    batch in place of `batches`; `grids`: the work-group counts of both passes in
+    place of `grids1` and `grids2`."""
+    if batch is not None:
+        batches = (batch,)
+    if grids is not None:
+        grids1 = grids2 = grids
     dev = torch.device("cuda", device)
     pos, ten = _network(n_det, dev)
     gen = torch.Generator(device="cpu").manual_seed(1234)
     results, choices = [], {}
-    batch = max(batches)
+    most = max(batches)
     for n in lengths:
         cands = [p for p, d in fcas.plans() if d["n"] == n]
         if not cands:
@@ -87,15 +94,15 @@ def autotune(lengths=DEFAULT_LENGTHS, n_det=4, fs=2048.0, batches=(16, 256), rep
         xf = torch.complex(torch.randn(n_det, half, generator=gen, dtype=torch.float64),
                            torch.randn(n_det, half, generator=gen, dtype=torch.float64)).to(dev)
         psd = torch.ones(n_det, half, dtype=torch.float64, device=dev)
-        u = torch.rand(batch, 4, generator=gen, dtype=torch.float64)
+        u = torch.rand(most, 4, generator=gen, dtype=torch.float64)
         lo, hi = torch.tensor(BOX_LO, dtype=torch.float64), torch.tensor(BOX_HI, dtype=torch.float64)
         theta = (lo + u * (hi - lo)).to(dev)
-        seg = torch.zeros(batch, dtype=torch.int32, device=dev)
+        seg = torch.zeros(most, dtype=torch.int32, device=dev)
         # the long three-pass lengths are timed with the 4 GiB workspace their
         # searches use (36 hour-long points per launch, measured fastest)
-        ws = min(4 << 30, batch * 2 * n * 8) if n > 262144 else 0
+        ws = min(4 << 30, most * 2 * n * 8) if n > 262144 else 0
         ctx = fcas.Context(pos, ten, fs=fs, f_low=30.0, f_high=1000.0, box_lo=BOX_LO, box_hi=BOX_HI,
-                           max_batch=batch, max_samples=n, device=device, tuning=None, workspace_bytes=ws)
+                           max_batch=most, max_samples=n, device=device, tuning=None, workspace_bytes=ws)
         best = None
         for p in cands:
             for g1 in grids1:
@@ -109,7 +116,7 @@ def autotune(lengths=DEFAULT_LENGTHS, n_det=4, fs=2048.0, batches=(16, 256), rep
         ctx.close()
         choices[str(n)] = best
         log(f"N={n}: chose {best}")
-    doc = dict(device=torch.cuda.get_device_name(dev), n_det=n_det, batches=list(batches), reps=reps,
+    doc = dict(device=torch.cuda.get_device_name(dev), n_det=n_det, batch=most, batches=list(batches), reps=reps,
                what="mean device time of one fitness call (set-up, passes, finalize), geometric mean over the batches",
                written=time.strftime("%Y-%m-%d %H:%M:%S"), choices=choices, measurements=results)
     if out:
