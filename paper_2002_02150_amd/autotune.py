@@ -72,6 +72,32 @@ def time_plan(ctx, plan, g1, g2, xf, psd, theta, seg, reps):
     return min(samples)
 
 
+def rank(plans, grids1, grids2, batches, time, log=lambda s: None):
+    """The choice of least geometric mean over the batches, and every
+    measurement, of `plans` ([(plan, its dict)]), time(plan, grid1, grid2, batch)
+    in ms.  A batch that gives each pass-1 tile of every point a work-group of
+    its own (up to 1024 of them) does not use grid1: it is timed once per plan
+    and grid2, so that noise between equal calls ranks nothing."""
+    best, results, legs = None, [], {}
+    for p, d in plans:
+        tiles1 = d["n2"] // d["cols"]
+        uses = [m for m in batches if m * tiles1 > 1024]
+        for g1 in grids1 if uses else (max(grids1),):
+            for g2 in grids2:
+                each = []
+                for m in batches:
+                    at = g1 if m in uses else max(grids1)
+                    if (p, at, g2, m) not in legs:
+                        legs[p, at, g2, m] = time(p, at, g2, m)
+                    each.append(legs[p, at, g2, m])
+                ms = math.exp(sum(math.log(t) for t in each) / len(each))
+                results.append(dict(plan=p, grid1=g1, grid2=g2, ms=ms, each=each))
+                if best is None or ms < best["ms"]:
+                    best = dict(plan=p, grid1=g1, grid2=g2, ms=ms)
+        log(f"plan {p}: best so far {best}")
+    return best, results
+
+
 def autotune(lengths=DEFAULT_LENGTHS, n_det=4, fs=2048.0, batch=None, reps=10, grids=None, out=fcas.TUNING_PATH,
              device=0, log=print, batches=(16, 256), grids1=GRIDS1, grids2=GRIDS2):
     """Times the plans of `lengths` and writes the choices to `out`.  `batch`: one
@@ -87,8 +113,8 @@ def autotune(lengths=DEFAULT_LENGTHS, n_det=4, fs=2048.0, batch=None, reps=10, g
     results, choices = [], {}
     most = max(batches)
     for n in lengths:
-        cands = [p for p, d in fcas.plans() if d["n"] == n]
-        if not cands:
+        plans = [(p, d) for p, d in fcas.plans() if d["n"] == n]
+        if not plans:
             continue
         half = n // 2 + 1
         xf = torch.complex(torch.randn(n_det, half, generator=gen, dtype=torch.float64),
@@ -103,16 +129,10 @@ def autotune(lengths=DEFAULT_LENGTHS, n_det=4, fs=2048.0, batch=None, reps=10, g
         ws = min(4 << 30, most * 2 * n * 8) if n > 262144 else 0
         ctx = fcas.Context(pos, ten, fs=fs, f_low=30.0, f_high=1000.0, box_lo=BOX_LO, box_hi=BOX_HI,
                            max_batch=most, max_samples=n, device=device, tuning=None, workspace_bytes=ws)
-        best = None
-        for p in cands:
-            for g1 in grids1:
-                for g2 in grids2:
-                    each = [time_plan(ctx, p, g1, g2, xf, psd, theta[:m], seg[:m], reps) for m in batches]
-                    ms = math.exp(sum(math.log(t) for t in each) / len(each))
-                    results.append(dict(n=n, plan=p, grid1=g1, grid2=g2, ms=ms, each=each))
-                    if best is None or ms < best["ms"]:
-                        best = dict(plan=p, grid1=g1, grid2=g2, ms=ms)
-            log(f"N={n} plan {p}: best so far {best}")
+        best, measured = rank(plans, grids1, grids2, batches,
+                              lambda p, g1, g2, m: time_plan(ctx, p, g1, g2, xf, psd, theta[:m], seg[:m], reps),
+                              lambda t: log(f"N={n} {t}"))
+        results += [dict(n=n, **r) for r in measured]
         ctx.close()
         choices[str(n)] = best
         log(f"N={n}: chose {best}")
