@@ -7,6 +7,8 @@
 // usage: fcas_emu <precision 0|1> <plan> <n_det> <k_lo> <k_hi> <df> <f_star> <in_prefix> <out_file>
 //   inputs  <in_prefix>.{pos,ten,sigma,b,theta} float64, <in_prefix>.y complex64 or complex128 [K][n_det]
 //   output  N float64 Gamma^2_j, then best value, best sample (float64)
+//   FCAS_EMU_ROW=d in the environment plants a mistake: pass 2 takes the
+//   factors of row j1 + d (mod N1) for row j1
 #include <algorithm>
 #include <array>
 #include <cstdio>
@@ -37,24 +39,42 @@ struct Regs {
   cplx<Real> v[2][E];
 };
 
-// All stages of a length-L transform for `nt` threads sharing one LDS buffer
-// per transform: buffer of thread `tid` is bufs[owner(tid)], index t = pos(tid).
-template <typename Real, int L, int E, class Rad, int I, int Ns, bool HALF, int PAD, class Owner, class Pos>
-static void emu_stages(std::vector<Regs<Real, E>>& regs, std::vector<std::vector<cplx<Real>>>& bufs,
-                       const std::vector<cplx<Real>>& tw, Owner owner, Pos pos) {
+// All stages of a length-L transform for the threads of a work-group sharing
+// one LDS buffer per transform: buffer of thread `tid` is bufs[owner(tid)],
+// index t = pos(tid).  Passes 1 and 2: factors in registers (one GeoSet per
+// thread); the middle pass: a table of twiddles.
+template <typename Real, int L, int E, class Rad, int I, bool SHIFT, bool HALF, int PAD, class Owner, class Pos>
+static void emu_geo_stages(std::vector<Regs<Real, E>>& regs, std::vector<std::vector<cplx<Real>>>& bufs,
+                           const std::vector<GeoSet<Real, L, E, Rad, SHIFT>>& geo, Owner owner, Pos pos) {
+  if constexpr (I < Rad::count) {
+    for (int s = 0; s < 2; ++s) {
+      for (size_t tid = 0; tid < regs.size(); ++tid)
+        geo_stage<Real, L, E, Rad, I, SHIFT, HALF && I == 0, PAD>(regs[tid].v[s], bufs[owner(tid)].data(), geo[tid],
+                                                                  pos(tid));
+      if constexpr (I < Rad::count - 1)
+        for (size_t tid = 0; tid < regs.size(); ++tid)
+          stage_gather<Real, L, E, PAD>(regs[tid].v[s], bufs[owner(tid)].data(), pos(tid));
+    }
+    emu_geo_stages<Real, L, E, Rad, I + 1, SHIFT, HALF, PAD>(regs, bufs, geo, owner, pos);
+  }
+}
+
+template <typename Real, int L, int E, class Rad, int I, int Ns, int PAD, class Owner, class Pos>
+static void emu_table_stages(std::vector<Regs<Real, E>>& regs, std::vector<std::vector<cplx<Real>>>& bufs,
+                             const std::vector<cplx<Real>>& tw, Owner owner, Pos pos) {
   if constexpr (I < Rad::count) {
     constexpr int R = Rad::value[I];
     constexpr bool LAST = (I == Rad::count - 1);
     for (int s = 0; s < 2; ++s) {
       for (size_t tid = 0; tid < regs.size(); ++tid)
-        stage_butterflies<Real, L, E, R, Ns, LAST, HALF && I == 0, PAD>(regs[tid].v[s], bufs[owner(tid)].data(),
-                                                                       tw.data(), pos(tid));
+        stage_butterflies<Real, L, E, R, Ns, LAST, false, PAD>(regs[tid].v[s], bufs[owner(tid)].data(), tw.data(),
+                                                               pos(tid));
       if constexpr (!LAST) {
         for (size_t tid = 0; tid < regs.size(); ++tid)
           stage_gather<Real, L, E, PAD>(regs[tid].v[s], bufs[owner(tid)].data(), pos(tid));
       }
     }
-    emu_stages<Real, L, E, Rad, I + 1, Ns * R, false, PAD>(regs, bufs, tw, owner, pos);
+    emu_table_stages<Real, L, E, Rad, I + 1, Ns * R, PAD>(regs, bufs, tw, owner, pos);
   }
 }
 
@@ -70,22 +90,45 @@ static void prologue(cplx<Real> (&v)[2][PL::E1], const EvalDesc& ev, const SegDe
   }
 }
 
-template <typename Real, class PL, int DT>
+// The prologue of one thread for n_det detectors (as in the kernels, a
+// compile-time count; `loop`: the run-time loop of the fused kernel).
+template <typename Real, class PL>
+static void any_prologue(cplx<Real> (&v)[2][PL::E1], const EvalDesc& ev, const SegDesc& sg, int n_det, bool loop,
+                         int tile, int c, int p) {
+  switch (loop ? 0 : n_det) {
+#define FCAS_EMU_DT(DT) \
+  case DT: return prologue<Real, PL, DT>(v, ev, sg, n_det, tile, c, p);
+    FCAS_EMU_DT(0) FCAS_EMU_DT(1) FCAS_EMU_DT(2) FCAS_EMU_DT(3) FCAS_EMU_DT(4)
+    FCAS_EMU_DT(5) FCAS_EMU_DT(6) FCAS_EMU_DT(7) FCAS_EMU_DT(8)
+  }
+}
+
+template <typename Real, class PL>
 static void run(const SegDesc& sg, const EvalDesc& ev, int n_det, std::vector<double>& series, double& bg,
                 int& bj) {
   const int64_t N = PL::N;
+  const int row_off = std::getenv("FCAS_EMU_ROW") ? std::atoi(std::getenv("FCAS_EMU_ROW")) : 0;
   std::vector<cplx<Real>> ws(2 * N);
-  std::vector<cplx<Real>> tw1(PL::N1), tw2(PL::N2);
-  for (int m = 0; m < PL::N1; ++m) tw1[m] = twiddle<Real>(m, PL::N1);
-  for (int m = 0; m < PL::N2; ++m) tw2[m] = twiddle<Real>(m, PL::N2);
   const int LP1 = lds_padded_len<kPad1>(PL::N1), LP2 = lds_padded_len<kPad2>(PL::N2);
+  using Geo1 = GeoSet<Real, PL::N1, PL::E1, typename PL::Rad1, false>;
+  using Geo2 = GeoSet<Real, PL::N2, PL::E2, typename PL::Rad2, !PL::THREE>;
+  std::vector<Geo1> geo1(PL::T1);
+  for (int tid = 0; tid < PL::T1; ++tid) geo1[tid].init(tid / PL::C);
   for (int tile = 0; tile < PL::TILES1; ++tile) {
-    std::vector<Regs<Real, PL::E1>> regs(PL::T1);
+    std::vector<Regs<Real, PL::E1>> regs(PL::T1), looped(PL::T1);
     std::vector<std::vector<cplx<Real>>> bufs(PL::C, std::vector<cplx<Real>>(LP1));
-    for (int tid = 0; tid < PL::T1; ++tid)
-      prologue<Real, PL, DT>(regs[tid].v, ev, sg, n_det, tile, tid % PL::C, tid / PL::C);
-    emu_stages<Real, PL::N1, PL::E1, typename PL::Rad1, 0, 1, true, kPad1>(
-        regs, bufs, tw1, [](size_t t) { return (int)(t % PL::C); }, [](size_t t) { return (int)(t / PL::C); });
+    for (int tid = 0; tid < PL::T1; ++tid) {
+      any_prologue<Real, PL>(regs[tid].v, ev, sg, n_det, false, tile, tid % PL::C, tid / PL::C);
+      any_prologue<Real, PL>(looped[tid].v, ev, sg, n_det, true, tile, tid % PL::C, tid / PL::C);
+      for (int s = 0; s < 2; ++s)
+        for (int q = 0; q < PL::E1 / 2; ++q)
+          if (regs[tid].v[s][q].x != looped[tid].v[s][q].x || regs[tid].v[s][q].y != looped[tid].v[s][q].y) {
+            std::fprintf(stderr, "the two prologues differ at tile %d thread %d\n", tile, tid);
+            std::exit(8);
+          }
+    }
+    emu_geo_stages<Real, PL::N1, PL::E1, typename PL::Rad1, 0, false, true, kPad1>(
+        regs, bufs, geo1, [](size_t t) { return (int)(t % PL::C); }, [](size_t t) { return (int)(t / PL::C); });
     for (int tid = 0; tid < PL::T1; ++tid) pass1_store<Real, PL>(regs[tid].v, ws.data(), tile, tid % PL::C, tid / PL::C);
   }
   if constexpr (PL::THREE) {
@@ -99,7 +142,7 @@ static void run(const SegDesc& sg, const EvalDesc& ev, int n_det, std::vector<do
         passm_fetch<Real, PL>(regs[tid].v, ws.data(), tile, tid % PL::CM, tid / PL::CM);
         passm_twiddle_in<Real, PL>(regs[tid].v, tile, tid % PL::CM, tid / PL::CM);
       }
-      emu_stages<Real, PL::NM, PL::EM, typename PL::RadM, 0, 1, false, kPadM>(
+      emu_table_stages<Real, PL::NM, PL::EM, typename PL::RadM, 0, 1, kPadM>(
           regs, bufs, twm, [](size_t t) { return (int)(t % PL::CM); }, [](size_t t) { return (int)(t / PL::CM); });
       for (int tid = 0; tid < PL::TM; ++tid) {
         passm_twiddle_out<Real, PL>(regs[tid].v, tile, tid % PL::CM, tid / PL::CM);
@@ -113,10 +156,15 @@ static void run(const SegDesc& sg, const EvalDesc& ev, int n_det, std::vector<do
   for (int tile = 0; tile < PL::TILES2; ++tile) {
     std::vector<Regs<Real, PL::E2>> regs(PL::T2);
     std::vector<std::vector<cplx<Real>>> bufs(PL::RW, std::vector<cplx<Real>>(LP2));
-    for (int tid = 0; tid < PL::T2; ++tid)
-      pass2_load<Real, PL>(regs[tid].v, ws.data(), tile, tid / PL::P2, tid % PL::P2);
-    emu_stages<Real, PL::N2, PL::E2, typename PL::Rad2, 0, 1, false, kPad2>(
-        regs, bufs, tw2, [](size_t t) { return (int)(t / PL::P2); }, [](size_t t) { return (int)(t % PL::P2); });
+    std::vector<Geo2> geo2(PL::T2);
+    for (int tid = 0; tid < PL::T2; ++tid) {
+      const int r = tid / PL::P2, p = tid % PL::P2;
+      pass2_fetch<Real, PL>(regs[tid].v, ws.data(), tile, r, p);
+      if (PL::THREE) geo2[tid].init(p);
+      else geo2[tid].init(p, (tile * PL::RW + r + row_off) % PL::N1, PL::N1);
+    }
+    emu_geo_stages<Real, PL::N2, PL::E2, typename PL::Rad2, 0, !PL::THREE, false, kPad2>(
+        regs, bufs, geo2, [](size_t t) { return (int)(t / PL::P2); }, [](size_t t) { return (int)(t % PL::P2); });
     for (int tid = 0; tid < PL::T2; ++tid) {
       const int r = tid / PL::P2, p = tid % PL::P2;
       const int j0 = row_base<PL>(tile * PL::RW + r);
@@ -125,9 +173,10 @@ static void run(const SegDesc& sg, const EvalDesc& ev, int n_det, std::vector<do
         if (series.at(j) != -1.0) { std::fprintf(stderr, "sample %lld written twice\n", (long long)j); std::exit(4); }
         series.at(j) = (double)(norm2(regs[tid].v[0][q]) + norm2(regs[tid].v[1][q]));
       }
-      Real g;
+      Real gs[PL::E2], g;
       int j;
-      pass2_best<Real, PL>(regs[tid].v, tile, r, p, g, j);
+      for (int q = 0; q < PL::E2; ++q) gs[q] = norm2(regs[tid].v[0][q]) + norm2(regs[tid].v[1][q]);
+      pass2_best_of<Real, PL>(gs, tile, r, p, g, j, 0, N);
       if (better((double)g, j, bg, bj)) { bg = (double)g; bj = j; }
     }
   }
@@ -173,11 +222,7 @@ static int main_t(int plan, int n_det, int k_lo, int k_hi, double df, double f_s
 #define FCAS_EMU_CASE(id, ...)                                                                         \
   case id: {                                                                                           \
     using PL = std::conditional_t<std::is_same_v<Real, float>, PlanF##id, PlanD##id>;                  \
-    if (n_det == 1) run<Real, PL, 1>(sg, ev, n_det, series, bg, bj);                                   \
-    else if (n_det == 2) run<Real, PL, 2>(sg, ev, n_det, series, bg, bj);                              \
-    else if (n_det == 3) run<Real, PL, 3>(sg, ev, n_det, series, bg, bj);                              \
-    else if (n_det == 4) run<Real, PL, 4>(sg, ev, n_det, series, bg, bj);                              \
-    else run<Real, PL, 0>(sg, ev, n_det, series, bg, bj);                                              \
+    run<Real, PL>(sg, ev, n_det, series, bg, bj);                                                      \
     break;                                                                                             \
   }
   switch (plan) {
