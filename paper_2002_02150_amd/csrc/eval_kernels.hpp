@@ -103,38 +103,23 @@ __device__ __forceinline__ void lds_exchange_sync() {
   }
 }
 
-// All stages of the S series (1 or 2) of one transform held in registers;
-// JOINT: two series exchange through LDS together (buf0, buf1), else they take
-// turns in buf0.
-template <typename Real, class PL, int L, int E, class Rad, int I, int Ns, bool HALF, bool WAVE, int PAD,
-          bool JOINT, int S>
-__device__ __forceinline__ void run_stages(cplx<Real> (&v)[S][E], cplx<Real>* buf0, cplx<Real>* buf1,
-                                           const cplx<Real>* tw, int t) {
+// All stages of the middle pass for the S series (1 or 2) of one transform held
+// in registers, which take turns in the LDS buffer.
+template <typename Real, int L, int E, class Rad, int I, int Ns, int PAD, int S>
+__device__ __forceinline__ void run_stages(cplx<Real> (&v)[S][E], cplx<Real>* buf, const cplx<Real>* tw, int t) {
   if constexpr (I < Rad::count) {
     constexpr int R = Rad::value[I];
     constexpr bool LAST = (I == Rad::count - 1);
-    static_assert(!JOINT || S == 2, "a joint exchange needs both series");
-    if constexpr (JOINT) {
-      stage_butterflies<Real, L, E, R, Ns, LAST, HALF && I == 0, PAD>(v[0], buf0, tw, t);
-      stage_butterflies<Real, L, E, R, Ns, LAST, HALF && I == 0, PAD>(v[1], buf1, tw, t);
-      if constexpr (!LAST) {
-        lds_exchange_sync<WAVE>();
-        stage_gather<Real, L, E, PAD>(v[0], buf0, t);
-        stage_gather<Real, L, E, PAD>(v[1], buf1, t);
-        lds_exchange_sync<WAVE>();
-      }
-    } else {
 #pragma unroll
-      for (int s = 0; s < S; ++s) {
-        stage_butterflies<Real, L, E, R, Ns, LAST, HALF && I == 0, PAD>(v[s], buf0, tw, t);
-        if constexpr (!LAST) {
-          lds_exchange_sync<WAVE>();
-          stage_gather<Real, L, E, PAD>(v[s], buf0, t);
-          lds_exchange_sync<WAVE>();
-        }
+    for (int s = 0; s < S; ++s) {
+      stage_butterflies<Real, L, E, R, Ns, LAST, PAD>(v[s], buf, tw, t);
+      if constexpr (!LAST) {
+        __syncthreads();
+        stage_gather<Real, L, E, PAD>(v[s], buf, t);
+        __syncthreads();
       }
     }
-    run_stages<Real, PL, L, E, Rad, I + 1, Ns * R, false, WAVE, PAD, JOINT, S>(v, buf0, buf1, tw, t);
+    run_stages<Real, L, E, Rad, I + 1, Ns * R, PAD, S>(v, buf, tw, t);
   }
 }
 
@@ -313,17 +298,14 @@ __global__ void __launch_bounds__(PL::T1)
 // one pass-1 row, so every load and store instruction moves CM * 8 bytes of
 // contiguous row per transform element (128 bytes at CM = 16).
 // ---------------------------------------------------------------------------
-// Exchange mode, series per work item and software prefetch of the middle
-// pass.  Measured on the hour-long plans: the series taking turns in LDS (half
-// the LDS) runs 1.75x faster than both at once; a second register set for
-// prefetching then gains nothing, and neither does one series per work item
-// (117 instead of 240 VGPRs, twice the waves per SIMD, 4% slower): the pass
-// moves its 32 N bytes per point at the rate of a device copy.
-constexpr bool kPassmJoint = false;
+// Series per work item and software prefetch of the middle pass.  Measured on
+// the hour-long plans: the series taking turns in LDS (half the LDS) runs 1.75x
+// faster than both at once; a second register set for prefetching then gains
+// nothing, and neither does one series per work item (117 instead of 240 VGPRs,
+// twice the waves per SIMD, 4% slower): the pass moves its 32 N bytes per point
+// at the rate of a device copy.
 constexpr int kPassmSeries = 2;         // series per work item (1: each series its own item)
 constexpr bool kPassmPrefetch = false;
-template <typename Real>
-constexpr bool kPassmJointFor = kPassmJoint && sizeof(Real) == 4 && kPassmSeries == 2;
 
 // Work item -> (list position in the launch, first series, tile); the items
 // of one point run series by series, tiles in order.
@@ -347,13 +329,11 @@ __device__ __forceinline__ void passm_fetch_item(cplx<Real> (&v)[kPassmSeries][P
 
 template <typename Real, class PL>
 __device__ __forceinline__ void passm_item(cplx<Real> (&v)[kPassmSeries][PL::EM], const PassArgs& a, int item,
-                                           cplx<Real>* buf0, cplx<Real>* buf1, const cplx<Real>* tw, int c, int p) {
+                                           cplx<Real>* buf, const cplx<Real>* tw, int c, int p) {
   int slot, s0, tile;
   passm_decode<PL>(item, slot, s0, tile);
   passm_twiddle_in<Real, PL>(v, tile, c, p);
-  run_stages<Real, PL, PL::NM, PL::EM, typename PL::RadM, 0, 1, false, false, kPadM, kPassmJointFor<Real>,
-             kPassmSeries>(
-      v, buf0, buf1, tw, p);
+  run_stages<Real, PL::NM, PL::EM, typename PL::RadM, 0, 1, kPadM>(v, buf, tw, p);
   passm_twiddle_out<Real, PL>(v, tile, c, p);
   passm_store<Real, PL>(v, (cplx<Real>*)a.ws + (int64_t)slot * 2 * PL::N, tile, c, p, s0);
 }
@@ -369,8 +349,7 @@ __device__ __forceinline__ void passm_body(const PassArgs& a, cplx<Real>* lds, c
   const int tid = threadIdx.x;
   const int items = launch_span(a) * (2 / kPassmSeries) * PL::TILESM;
   const int c = tid % PL::CM, p = tid / PL::CM;
-  cplx<Real>* buf0 = lds + c * LP;
-  cplx<Real>* buf1 = kPassmJointFor<Real> ? lds + (PL::CM + c) * LP : buf0;
+  cplx<Real>* buf = lds + c * LP;
   if constexpr (kPassmPrefetch) {
     cplx<Real> va[kPassmSeries][PL::EM], vb[kPassmSeries][PL::EM];
     int item = block;
@@ -378,17 +357,17 @@ __device__ __forceinline__ void passm_body(const PassArgs& a, cplx<Real>* lds, c
     while (item < items) {
       const int next = item + nblocks;
       if (next < items) passm_fetch_item<Real, PL>(vb, a, next, c, p);
-      passm_item<Real, PL>(va, a, item, buf0, buf1, tw, c, p);
+      passm_item<Real, PL>(va, a, item, buf, tw, c, p);
       if (next >= items) break;
       item = next + nblocks;
       if (item < items) passm_fetch_item<Real, PL>(va, a, item, c, p);
-      passm_item<Real, PL>(vb, a, next, buf0, buf1, tw, c, p);
+      passm_item<Real, PL>(vb, a, next, buf, tw, c, p);
     }
   } else {
     for (int item = block; item < items; item += nblocks) {
       cplx<Real> v[kPassmSeries][PL::EM];
       passm_fetch_item<Real, PL>(v, a, item, c, p);
-      passm_item<Real, PL>(v, a, item, buf0, buf1, tw, c, p);
+      passm_item<Real, PL>(v, a, item, buf, tw, c, p);
     }
   }
 }
@@ -396,7 +375,7 @@ __device__ __forceinline__ void passm_body(const PassArgs& a, cplx<Real>* lds, c
 template <typename Real, class PL>
 __global__ void __launch_bounds__(PL::TM) k_passm(PassArgs a) {
   static_assert(PL::THREE, "two-pass plans have no middle pass");
-  __shared__ cplx<Real> lds[(kPassmJointFor<Real> ? 2 : 1) * PL::CM * lds_padded_len<kPadM>(PL::NM)];
+  __shared__ cplx<Real> lds[PL::CM * lds_padded_len<kPadM>(PL::NM)];
   __shared__ cplx<Real> tw[PL::NM];
   init_twiddles<Real, PL::NM, PL::TM>(tw);
   passm_body<Real, PL>(a, lds, tw, blockIdx.x, gridDim.x);

@@ -267,52 +267,27 @@ template <> FCAS_HD cplx<double> ramp_step<double>(const EvalDesc& e, int i) {
   return mk<double>(e.step1[i][0], e.step1[i][1]);
 }
 
-// W_0(k), W_1(k) for one in-band bin.  kk = k - k_lo.
-template <typename Real>
-FCAS_HD void project_bin(const EvalDesc& ev, const cplx<Real>* y, const double* bt, int n_det, int k,
-                         int kk, cplx<Real>& w0, cplx<Real>& w1) {
-  const double phc = common_phase(ev.coef, bt[kk]);
-  const double kd = (double)k;
-  const cplx<Real>* yr = y + (int64_t)kk * n_det;
-  w0 = mk<Real>(0, 0);
-  w1 = mk<Real>(0, 0);
-  for (int i = 0; i < n_det; ++i) {
-    const double ph = kd * ev.dly[i] + phc;   // cycles
-    const double r = ph - rint(ph);           // reduced to [-1/2, 1/2] in FP64
-    Real s, c;
-    sincos_rev((Real)r, &s, &c);
-    const cplx<Real> w = mul(yr[i], mk<Real>(c, s));
-    const Real q0 = Basis<Real>::get(ev, i, 0), q1 = Basis<Real>::get(ev, i, 1);
-    w0 = mk<Real>(w0.x + q0 * w.x, w0.y + q0 * w.y);
-    w1 = mk<Real>(w1.x + q1 * w.x, w1.y + q1 * w.y);
-  }
-}
-
 // ---------------------------------------------------------------------------
-// One Stockham stage for one series of one transform (see fft_core.hpp).
-// Either leaves the outputs in registers (last stage) or scatters them to the
+// One Stockham stage of the middle pass for one series of one transform (see
+// fft_core.hpp), twiddles from a table.  Either leaves the outputs in registers (last stage) or scatters them to the
 // transform's LDS buffer, to be gathered back in natural strided order.
 // ---------------------------------------------------------------------------
-template <typename Real, int L, int E, int R, int Ns, bool LAST, bool HALF, int PAD>
+template <typename Real, int L, int E, int R, int Ns, bool LAST, int PAD>
 FCAS_HD void stage_butterflies(cplx<Real>* vs, cplx<Real>* buf, const cplx<Real>* tw, int t) {
   constexpr int P = L / E;
   constexpr int B = E / R;
   static_assert(E % R == 0, "radix must divide the elements per thread");
-  static_assert(!HALF || (Ns == 1 && B == 1), "half-zero inputs only in a first stage with one butterfly");
 #pragma unroll
   for (int b = 0; b < B; ++b) {
     const int v = t + b * P;
     cplx<Real> x[R];
 #pragma unroll
-    for (int p = 0; p < (HALF ? R / 2 : R); ++p) x[p] = vs[b + p * B];
+    for (int p = 0; p < R; ++p) x[p] = vs[b + p * B];
     if constexpr (Ns > 1) {
 #pragma unroll
       for (int p = 1; p < R; ++p) x[p] = mul(x[p], tw[stockham_tw(v, Ns, R, p, L)]);
     }
-    if constexpr (HALF)
-      dft_half<R>(x);
-    else
-      dft<R>(x);
+    dft<R>(x);
     if constexpr (LAST) {
 #pragma unroll
       for (int p = 0; p < R; ++p) vs[b + p * B] = x[p];
@@ -764,9 +739,9 @@ FCAS_HD void passm_store(cplx<Real> (&v)[S][PL::EM], cplx<Real>* slot, int tile,
 }
 
 // Pass 2 prologue: thread (r, p) of row tile `tile` reads row tile RW + r,
-// register q holds k2 = p + q P2 (pass2_fetch); in a two-pass plan the row is
-// j1 and the four-step twiddle w_N^{k2 j1} follows (pass2_twiddle), in a
-// three-pass plan the middle pass has applied it.
+// register q holds k2 = p + q P2.  In a two-pass plan the row is j1, and the
+// four-step twiddle w_N^{k2 j1} is the shift of the row's transform (GeoSet);
+// in a three-pass plan the middle pass has applied it.
 template <typename Real, class PL>
 FCAS_HD void pass2_fetch(cplx<Real> (&v)[2][PL::E2], const cplx<Real>* slot, int tile, int r, int p) {
   const int j1 = tile * PL::RW + r;
@@ -777,28 +752,6 @@ FCAS_HD void pass2_fetch(cplx<Real> (&v)[2][PL::E2], const cplx<Real>* slot, int
     v[0][q] = stream_load(slot + row + k2);
     v[1][q] = stream_load(slot + PL::N + row + k2);
   }
-}
-
-// w_N^{k2 j1} for k2 = p + q P2: exact (one sine/cosine pair) at q = 0, then
-// advanced by the factor w_N^{P2 j1} from register to register.
-template <typename Real, class PL>
-FCAS_HD void pass2_twiddle(cplx<Real> (&v)[2][PL::E2], int tile, int r, int p) {
-  static_assert(!PL::THREE, "three-pass plans twiddle in the middle pass");
-  const int j1 = tile * PL::RW + r;
-  cplx<Real> t = twiddle<Real>(p * j1, (int)PL::N);                // p j1 < N
-  const cplx<Real> st = twiddle<Real>(PL::P2 * j1, (int)PL::N);    // P2 j1 < N
-#pragma unroll
-  for (int q = 0; q < PL::E2; ++q) {
-    v[0][q] = mul(v[0][q], t);
-    v[1][q] = mul(v[1][q], t);
-    if (q + 1 < PL::E2) t = mul(t, st);
-  }
-}
-
-template <typename Real, class PL>
-FCAS_HD void pass2_load(cplx<Real> (&v)[2][PL::E2], const cplx<Real>* slot, int tile, int r, int p) {
-  pass2_fetch<Real, PL>(v, slot, tile, r, p);
-  if constexpr (!PL::THREE) pass2_twiddle<Real, PL>(v, tile, r, p);
 }
 
 // Pass 2 epilogue: Gamma^2_j = |a_0|^2 + |a_1|^2 (g) at j = row_base + ROWS2 (p + q P2),
@@ -820,14 +773,6 @@ FCAS_HD void pass2_best_of(const Real (&g)[PL::E2], int tile, int r, int p, Real
       best_j = j;
     }
   }
-}
-template <typename Real, class PL>
-FCAS_HD void pass2_best(const cplx<Real> (&v)[2][PL::E2], int tile, int r, int p, Real& best, int& best_j,
-                        int64_t j_lo = 0, int64_t j_hi = PL::N) {
-  Real g[PL::E2];
-#pragma unroll
-  for (int q = 0; q < PL::E2; ++q) g[q] = norm2(v[0][q]) + norm2(v[1][q]);
-  pass2_best_of<Real, PL>(g, tile, r, p, best, best_j, j_lo, j_hi);
 }
 
 // Work item `item` of the fused schedule (cnt evaluations, lag L, T1 pass-1

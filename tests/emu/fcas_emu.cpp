@@ -67,8 +67,7 @@ static void emu_table_stages(std::vector<Regs<Real, E>>& regs, std::vector<std::
     constexpr bool LAST = (I == Rad::count - 1);
     for (int s = 0; s < 2; ++s) {
       for (size_t tid = 0; tid < regs.size(); ++tid)
-        stage_butterflies<Real, L, E, R, Ns, LAST, false, PAD>(regs[tid].v[s], bufs[owner(tid)].data(), tw.data(),
-                                                               pos(tid));
+        stage_butterflies<Real, L, E, R, Ns, LAST, PAD>(regs[tid].v[s], bufs[owner(tid)].data(), tw.data(), pos(tid));
       if constexpr (!LAST) {
         for (size_t tid = 0; tid < regs.size(); ++tid)
           stage_gather<Real, L, E, PAD>(regs[tid].v[s], bufs[owner(tid)].data(), pos(tid));
