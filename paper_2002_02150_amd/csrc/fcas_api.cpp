@@ -510,14 +510,13 @@ EvalBufs own_bufs(const fcas_ctx* ctx) {
                   ctx->d_ws, ctx->ws_bytes, ctx->cfg.max_batch};
 }
 
-// Enqueues the per-point set-up: descriptors and, with build_lists, the
-// per-plan work lists (their counts are zero between calls: the context starts
+// Enqueues the per-point set-up: descriptors and the per-plan work lists (their counts are zero between calls: the context starts
 // with zeros and every finalize clears them once the passes are done).
 int enqueue_setup(fcas_ctx* ctx, const EvalBufs& b, int32_t n, const double* d_theta, const int32_t* d_seg,
-                  hipStream_t s, bool build_lists = true) {
+                  hipStream_t s) {
   hipError_t e;
   if ((e = launch_setup(ctx->d_net, ctx->d_segs, d_theta, d_seg, n, b.evals, b.lists, b.counts, b.list_stride,
-                        build_lists ? 1 : 0, ctx->d_err, s)) != hipSuccess)
+                        ctx->d_err, s)) != hipSuccess)
     return hip_fail(e, "set-up launch");
   return FCAS_OK;
 }

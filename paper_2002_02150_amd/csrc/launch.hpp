@@ -24,8 +24,8 @@ inline void launch_k(K kernel, dim3 grid, dim3 block, hipStream_t s, hipEvent_t 
 
 hipError_t launch_zero_i32(int32_t* p, int n, hipStream_t s);
 hipError_t launch_setup(const NetDesc* net, const SegDesc* segs, const double* theta, const int32_t* seg_ids,
-                        int n, EvalDesc* evals, int32_t* lists, int32_t* counts, int list_stride, int build_lists,
-                        int32_t* err, hipStream_t s);
+                        int n, EvalDesc* evals, int32_t* lists, int32_t* counts, int list_stride, int32_t* err,
+                        hipStream_t s);
 
 // fused persistent schedule (float plans)
 hipError_t launch_fused_f32(int plan, const FusedArgs& f, int grid, hipStream_t s);

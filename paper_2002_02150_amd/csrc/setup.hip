@@ -9,18 +9,16 @@ __global__ void k_zero_i32(int32_t* p, int n) {
   if (i < n) p[i] = 0;
 }
 
-// Eight lanes per point (setup_group).  With build_lists = 0 only the
-// descriptors are refreshed (the work lists and their counts are left alone).
+// Eight lanes per point (setup_group).
 __global__ void __launch_bounds__(64) k_setup(const NetDesc* __restrict__ netp, const SegDesc* __restrict__ segs,
                                               const double* __restrict__ theta, const int32_t* __restrict__ seg_ids,
                                               int n, EvalDesc* __restrict__ evals, int32_t* __restrict__ lists,
-                                              int32_t* __restrict__ counts, int list_stride, int build_lists,
+                                              int32_t* __restrict__ counts, int list_stride,
                                               int32_t* __restrict__ err) {
   const int e = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 3);
   const NetDesc& net = *netp;
   const SetupSeg q = setup_seg_load(net, segs, seg_ids, e, e < n);
-  setup_group(net, q, theta + 4 * (int64_t)(e < n ? e : 0), e, e < n, evals, lists, counts, list_stride, build_lists,
-              err);
+  setup_group(net, q, theta + 4 * (int64_t)(e < n ? e : 0), e, e < n, evals, lists, counts, list_stride, 1, err);
 }
 
 // sigma_i^2 = 4 df sum_{k in B} f_k^(-7/3) / S^i_k  (template norm, Sec. II.D).
@@ -70,11 +68,11 @@ hipError_t launch_zero_i32(int32_t* p, int n, hipStream_t s) {
 }
 
 hipError_t launch_setup(const NetDesc* net, const SegDesc* segs, const double* theta, const int32_t* seg_ids,
-                        int n, EvalDesc* evals, int32_t* lists, int32_t* counts, int list_stride, int build_lists,
-                        int32_t* err, hipStream_t s) {
+                        int n, EvalDesc* evals, int32_t* lists, int32_t* counts, int list_stride, int32_t* err,
+                        hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_setup, dim3((n + 7) / 8), dim3(64), 0, s, net, segs, theta, seg_ids, n, evals, lists,
-                     counts, list_stride, build_lists, err);
+                     counts, list_stride, err);
   return hipGetLastError();
 }
 
