@@ -205,7 +205,8 @@ int fitness_grad_batch(fcas_ctx* ctx, int32_t n, const double* d_theta, const in
  * one fitness batch, and moves each point to its best trial if that raises
  * Gamma^2.  d_theta float64 [n][4] is read and updated in place; d_fitness
  * float64 [n] and d_argmax int32 [n] receive Gamma^2 and j* at the final
- * points.  Needs n * n_trials <= max_batch, 1 <= n_trials <= 32. */
+ * points.  Needs n * n_trials <= max_batch, 1 <= n_trials <= 32.  With n_trials
+ * = 1 and n beyond half of max_batch, the points are taken in two halves. */
 int fitness_polish(fcas_ctx* ctx, int32_t n, double* d_theta, const int32_t* d_seg, int32_t n_steps,
                    double step_frac, int32_t n_trials, double* d_fitness, int32_t* d_argmax, void* hip_stream);
 

@@ -106,13 +106,14 @@ struct fcas_ctx {
   size_t ws_bytes = 0;
   void* d_scratch = nullptr;     // this device's copy of the static scratch array (not owned)
   GradBuffers grad{};
-  EvalDesc* d_pol_evals = nullptr; // [max_batch] polish: descriptors of the current points
+  EvalDesc* d_pol_evals = nullptr; // [pol_points] polish: descriptors of the current points
+  int pol_points = 0;              // points that a polish takes at a time
   double* d_pol_cand = nullptr;    // [max_batch][4] polish trials
   int plan_refs[kNumPlans] = {0};   // registered segments per plan
   int schedule = FCAS_SCHEDULE_FUSED;
   int n_cu = 0;                     // compute units of the device
   int fused_cap[kNumPlans] = {0};   // resident work-groups of each fused kernel (0 = not queried)
-  int32_t* d_done = nullptr;        // [kNumPlans][2][max_batch] fused-schedule tile counters
+  int32_t* d_done = nullptr;        // [plans it takes][2][max_batch] fused-schedule tile counters (null: takes none)
   bool timing = false;
   std::vector<TimedPair> t_pass1, t_passm, t_pass2, t_fused;
   int grid1[kNumPlans], grid2[kNumPlans];   // persistent grid sizes of the two passes
@@ -195,6 +196,21 @@ int free_all(fcas_ctx* c) {
   for (auto& t : c->t_pass2) { hipEventDestroy(t.a); hipEventDestroy(t.b); }
   for (auto& t : c->t_fused) { hipEventDestroy(t.a); hipEventDestroy(t.b); }
   return FCAS_OK;
+}
+
+// Whether the context takes points of `plan` through the fused schedule.
+bool runs_fused(const fcas_ctx* ctx, int plan) {
+  const PlanInfo& pi = kPlans[plan];
+  return ctx->schedule == FCAS_SCHEDULE_FUSED && pi.nm == 1 && pi.threads1[0] == pi.threads2[0] &&
+         fused_takes(pi.tiles1[0] + pi.tiles2[0]);
+}
+
+// How many plans before `plan` it takes so, of those its lengths admit: the
+// plan's place in d_done.
+int fused_rank(const fcas_ctx* ctx, int plan) {
+  int rank = 0;
+  for (int k = 0; k < plan; ++k) rank += kPlans[k].n <= ctx->cfg.max_samples && runs_fused(ctx, k);
+  return rank;
 }
 
 template <typename T>
@@ -298,6 +314,10 @@ int fcas_create(const fcas_network* net, const fcas_config* cfg, int device, fca
   c->seg_y.assign(cfg->max_segments, nullptr);
   c->seg_b.assign(cfg->max_segments, nullptr);
   const size_t part_elt = c->prec ? 8 : 4;
+  // a polish has at most max_batch trials: with two or more to a point, half as
+  // many descriptors hold its points; with one, half of its points at a time
+  c->pol_points = (B + 1) / 2;
+  const size_t done_bytes = sizeof(int32_t) * 2 * (size_t)fused_rank(c, kNumPlans) * B;
   for (int i = 0; i < kNumPlans; ++i)
     if (kPlans[i].n <= cfg->max_samples) c->part_stride = std::max(c->part_stride, kPlans[i].parts2[c->prec]);
   if ((rc = dev_alloc(&c->d_net, sizeof(NetDesc))) || (rc = dev_alloc(&c->d_segs, sizeof(SegDesc) * cfg->max_segments)) ||
@@ -312,10 +332,10 @@ int fcas_create(const fcas_network* net, const fcas_config* cfg, int device, fca
       (rc = dev_alloc(&c->d_err, sizeof(int32_t))) || (rc = dev_alloc(&c->d_sigma2, sizeof(double) * FCAS_MAX_DET)) ||
       (rc = dev_alloc(&c->d_inject, sizeof(double) * kInjectScratch)) ||
       (rc = dev_alloc(&c->d_ws, ws)) || (rc = alloc_grad_buffers(c->grad, B, net->n_det)) ||
-      (rc = dev_alloc(&c->d_pol_evals, sizeof(EvalDesc) * B)) ||
+      (rc = dev_alloc(&c->d_pol_evals, sizeof(EvalDesc) * c->pol_points)) ||
       (rc = dev_alloc(&c->d_pol_cand, sizeof(double) * 4 * B)) ||
       (rc = dev_alloc(&c->d_evaluated, sizeof(unsigned long long))) ||
-      (rc = dev_alloc(&c->d_done, sizeof(int32_t) * 2 * (size_t)kNumPlans * B))) {
+      (done_bytes && (rc = dev_alloc(&c->d_done, done_bytes)))) {
     std::string msg = g_last_error;
     free_all(c);
     delete c;
@@ -557,7 +577,7 @@ int enqueue_fused(fcas_ctx* ctx, const EvalBufs& b, int plan, int n, int cap, hi
   }
   FusedArgs f{};
   f.p = pass_args(ctx, b, plan, cap);
-  f.done1 = ctx->d_done + (size_t)plan * 2 * ctx->cfg.max_batch;
+  f.done1 = ctx->d_done + (size_t)fused_rank(ctx, plan) * 2 * ctx->cfg.max_batch;
   f.done2 = f.done1 + ctx->cfg.max_batch;
   f.err = ctx->d_err;
   f.lag = lag;
@@ -579,13 +599,6 @@ int enqueue_fused(fcas_ctx* ctx, const EvalBufs& b, int plan, int n, int cap, hi
 
 int enqueue_passes(fcas_ctx* ctx, const EvalBufs& b, int32_t n, double* d_fitness, int32_t* d_argmax,
                    hipStream_t s, bool fused_ok, bool timed, bool finalize = true);
-
-// Whether the context takes points of `plan` through the fused schedule.
-bool runs_fused(const fcas_ctx* ctx, int plan) {
-  const PlanInfo& pi = kPlans[plan];
-  return ctx->schedule == FCAS_SCHEDULE_FUSED && pi.nm == 1 && pi.threads1[0] == pi.threads2[0] &&
-         fused_takes(pi.tiles1[0] + pi.tiles2[0]);
-}
 
 // Points of a batch of n that one launch of `plan` takes: as many as the
 // workspace has slots.
@@ -669,7 +682,8 @@ int enqueue_passes(fcas_ctx* ctx, const EvalBufs& b, int32_t n, double* d_fitnes
   bool any_fused = false;
   for (int plan = 0; plan < kNumPlans; ++plan)
     any_fused = any_fused || (fused_ok && ctx->plan_refs[plan] > 0 && runs_fused(ctx, plan));
-  if (any_fused && (e = launch_zero_i32(ctx->d_done, 2 * kNumPlans * ctx->cfg.max_batch, s)) != hipSuccess)
+  if (any_fused &&
+      (e = launch_zero_i32(ctx->d_done, 2 * fused_rank(ctx, kNumPlans) * ctx->cfg.max_batch, s)) != hipSuccess)
     return hip_fail(e, "zero tile counters");
   const bool was_timing = ctx->timing;
   ctx->timing = was_timing && timed;
@@ -796,18 +810,14 @@ int fitness_grad_batch(fcas_ctx* ctx, int32_t n, const double* d_theta, const in
   return FCAS_OK;
 }
 
-int fitness_polish(fcas_ctx* ctx, int32_t n, double* d_theta, const int32_t* d_seg, int32_t n_steps,
-                   double step_frac, int32_t n_trials, double* d_fitness, int32_t* d_argmax, void* hip_stream) {
-  int rc = validate_batch(ctx, n, d_theta, d_seg, d_fitness, d_argmax);
-  if (rc) return rc;
-  if (n_steps < 0 || n_trials < 1 || n_trials > kMaxTrials) return fail(FCAS_EINVAL, "need n_steps >= 0, 1 <= n_trials <= 32");
-  if (!(step_frac > 0) || !std::isfinite(step_frac)) return fail(FCAS_EINVAL, "step_frac must be positive");
-  if ((int64_t)n * n_trials > ctx->cfg.max_batch)
-    return fail(FCAS_ECAPACITY, "n * n_trials = %lld exceeds max_batch = %d", (long long)n * n_trials,
-                ctx->cfg.max_batch);
-  if (n == 0) return FCAS_OK;
-  hipSetDevice(ctx->device);
-  hipStream_t s = (hipStream_t)hip_stream;
+}  // extern "C"
+
+namespace {
+
+// The polish of n points (at most pol_points).
+int enqueue_polish(fcas_ctx* ctx, int32_t n, double* d_theta, const int32_t* d_seg, int32_t n_steps, double step_frac,
+                   int32_t n_trials, double* d_fitness, int32_t* d_argmax, hipStream_t s) {
+  int rc;
   hipError_t e;
   // The points' descriptors are kept apart from those of the trials.
   EvalBufs points = own_bufs(ctx), b = own_bufs(ctx);
@@ -833,6 +843,29 @@ int fitness_polish(fcas_ctx* ctx, int32_t n, double* d_theta, const int32_t* d_s
       return hip_fail(e, "polish select launch");
     }
   }
+  return FCAS_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int fitness_polish(fcas_ctx* ctx, int32_t n, double* d_theta, const int32_t* d_seg, int32_t n_steps,
+                   double step_frac, int32_t n_trials, double* d_fitness, int32_t* d_argmax, void* hip_stream) {
+  int rc = validate_batch(ctx, n, d_theta, d_seg, d_fitness, d_argmax);
+  if (rc) return rc;
+  if (n_steps < 0 || n_trials < 1 || n_trials > kMaxTrials) return fail(FCAS_EINVAL, "need n_steps >= 0, 1 <= n_trials <= 32");
+  if (!(step_frac > 0) || !std::isfinite(step_frac)) return fail(FCAS_EINVAL, "step_frac must be positive");
+  if ((int64_t)n * n_trials > ctx->cfg.max_batch)
+    return fail(FCAS_ECAPACITY, "n * n_trials = %lld exceeds max_batch = %d", (long long)n * n_trials,
+                ctx->cfg.max_batch);
+  if (n == 0) return FCAS_OK;
+  hipSetDevice(ctx->device);
+  hipStream_t s = (hipStream_t)hip_stream;
+  for (int begin = 0; begin < n; begin += ctx->pol_points)
+    if ((rc = enqueue_polish(ctx, std::min(ctx->pol_points, n - begin), d_theta + 4 * (int64_t)begin, d_seg + begin,
+                             n_steps, step_frac, n_trials, d_fitness + begin, d_argmax + begin, s)))
+      return rc;
   return FCAS_OK;
 }
 
