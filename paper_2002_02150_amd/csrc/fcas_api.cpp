@@ -619,8 +619,8 @@ int direct_plan(const fcas_ctx* ctx, const EvalBufs& b, int n, bool fused_ok) {
     }
   if (only < 0 || kPlans[only].nm > 1 || points_per_launch(ctx, b, only, n) < n) return -1;
   if (fused_ok && runs_fused(ctx, only)) return -1;
-  return direct_call(n, kPlans[only].tiles1[ctx->prec], kPlans[only].threads1[ctx->prec], ctx->prec, ctx->n_cu) ? only
-                                                                                                               : -1;
+  const PlanInfo& pi = kPlans[only];
+  return direct_call(n, pi.tiles1[ctx->prec], pi.threads1[ctx->prec], ctx->prec, ctx->net.n_det, ctx->n_cu) ? only : -1;
 }
 
 // The passes of a direct call, and finalize.

@@ -30,16 +30,18 @@ inline StorePolicy store_policy(size_t bytes) {
 // gives every tile of every point a work-group): it saves the set-up kernel's
 // launch and the reads of its results, about 3 us, and repeats the set-up in
 // every work-group, which costs about as much once they no longer all start
-// together (16 wavefronts a CU for float, 12 for double, and never more than
-// four groups), or once more points than these add to one counter.  Measured,
-// direct / set-up kernel: float 131072 (256 threads) 0.88 at 256 work-groups,
-// 0.96 at 1024; 262144 (512 threads) 0.91 at 512, 1.02 at 640; 16384 0.93 at
-// 1024, 0.99 at 1280; double 131072 (256 threads) 0.95 at 768, 1.02 at 896;
-// 98304 (128 threads) 0.95 at 1024, 1.05 at 1152; 2048 (a work-group a point)
-// 0.96 at 384 points, 1.00 at 512, 1.21 at 1024 (double 0.98, 1.05, 1.07).
-inline bool direct_call(int points, int tiles, int threads, bool fp64, int n_cu) {
+// together (16 wavefronts a CU for float and for double of one or two
+// detectors, 12 for double of more, and never more than four groups), or once
+// more points than these add to one counter.  Measured, direct / set-up kernel,
+// four detectors unless said: float 131072 (256 threads) 0.88 at 256
+// work-groups, 0.96 at 1024; 262144 (512 threads) 0.91 at 512, 1.02 at 640; 16384
+// 0.93 at 1024, 0.99 at 1280; double 131072 (256 threads) 0.95 at 768, 1.02 at
+// 896 (two detectors 0.90 at 1024, 0.99 at 1152); 98304 (128 threads) 0.95 at
+// 1024, 1.05 at 1152; 2048 (a work-group a point) 0.96 at 384 points, 1.00 at
+// 512, 1.21 at 1024 (double 0.98, 1.05, 1.07); 4096 0.87 at 256 points, 0.98 at 512.
+inline bool direct_call(int points, int tiles, int threads, bool fp64, int n_det, int n_cu) {
   const long long groups = (long long)points * tiles;
-  return groups * (threads / 64) <= (fp64 ? 12 : 16) * n_cu && groups <= 4 * n_cu && 2 * points <= 3 * n_cu;
+  return groups * (threads / 64) <= (fp64 && n_det > 2 ? 12 : 16) * n_cu && groups <= 4 * n_cu && 4 * points <= 7 * n_cu;
 }
 
 // Whether the fused schedule takes a two-pass plan of so many work items

@@ -33,18 +33,20 @@ def test_store_policy(rule, nbytes, policy):
     assert rule("store", nbytes) == policy
 
 
-@pytest.mark.parametrize("points,tiles,threads,fp64,direct", [
-    (1, 32, 256, 0, 1), (32, 32, 256, 0, 1), (33, 32, 256, 0, 0),      # 131072 float: four groups a CU
-    (8, 64, 512, 0, 1), (9, 64, 512, 0, 0),                            # 262144 float: two of 512 threads
-    (2, 128, 1024, 0, 1), (3, 128, 1024, 0, 0),                        # one of 1024 threads
-    (12, 64, 256, 1, 1), (13, 64, 256, 1, 0),                          # 131072 double: three
-    (16, 64, 128, 1, 1), (17, 64, 128, 1, 0),                          # 98304 double: never more than four
-    (384, 1, 256, 0, 1), (385, 1, 256, 0, 0), (384, 1, 256, 1, 1), (385, 1, 256, 1, 0),   # 2048: points
-    (1 << 24, 256, 512, 0, 0),
+@pytest.mark.parametrize("points,tiles,threads,fp64,n_det,direct", [
+    (1, 32, 256, 0, 4, 1), (32, 32, 256, 0, 4, 1), (33, 32, 256, 0, 4, 0),      # 131072 float: four groups a CU
+    (8, 64, 512, 0, 4, 1), (9, 64, 512, 0, 4, 0), (9, 64, 512, 0, 1, 0),        # 262144 float: two of 512 threads
+    (2, 128, 1024, 0, 4, 1), (3, 128, 1024, 0, 4, 0),                           # one of 1024 threads
+    (12, 64, 256, 1, 3, 1), (13, 64, 256, 1, 3, 0), (13, 64, 256, 1, 8, 0),     # 131072 double: three,
+    (16, 64, 256, 1, 2, 1), (17, 64, 256, 1, 2, 0), (16, 64, 256, 1, 1, 1),     # four with up to two detectors
+    (16, 64, 128, 1, 4, 1), (17, 64, 128, 1, 4, 0),                             # 98304 double: never more than four
+    (448, 1, 256, 0, 4, 1), (449, 1, 256, 0, 4, 0), (448, 2, 256, 0, 6, 1),     # 2048 and 4096: points
+    (448, 1, 256, 1, 2, 1), (449, 1, 256, 1, 2, 0),
+    (1 << 24, 256, 512, 0, 4, 0),
 ])
-def test_direct_calls(rule, points, tiles, threads, fp64, direct):
+def test_direct_calls(rule, points, tiles, threads, fp64, n_det, direct):
     """A call sets its points up in pass 1 while its work-groups start together."""
-    assert rule("direct", points, tiles, threads, fp64, 256) == direct
+    assert rule("direct", points, tiles, threads, fp64, n_det, 256) == direct
 
 
 @pytest.mark.parametrize("items,fused", [(2, 1), (8, 1), (9, 0), (16, 0), (96, 0)])
