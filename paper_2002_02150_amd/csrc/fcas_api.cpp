@@ -712,7 +712,8 @@ int enqueue_passes(fcas_ctx* ctx, const EvalBufs& b, int32_t n, double* d_fitnes
            })) != hipSuccess)
         what = "pass-1 launch";
       if (!what && pi.nm > 1) {
-        const int gm = std::min(m * pi.tilesm[ctx->prec] * (2 / kPassmSeries), ctx->grid2[plan]);
+        const int gm = middle_groups((long long)m * pi.tilesm[ctx->prec] * (2 / kPassmSeries), ctx->grid2[plan],
+                                     ctx->prec);
         if ((e = timed_launch(ctx, ctx->t_passm, [&](hipEvent_t e0, hipEvent_t e1) {
                return launch_passm(ctx->prec, plan, a, gm, s, e0, e1);
              })) != hipSuccess)

@@ -52,4 +52,14 @@ inline bool direct_call(int points, int tiles, int threads, bool fp64, int n_det
 // where it costs least; longer points run as separate launches, same bits.
 inline bool fused_takes(int items) { return items <= 8; }
 
+// Work-groups of a three-pass plan's middle pass: at most one per item, and the
+// last pass's number for double.  Float takes at most 4096: beyond, the more
+// numerous work-groups of the last pass, which suit that one, cost it up to 12%
+// (us for 32 points of 3686400, 4096 / 16384 work-groups: middle 806 / 905, last
+// 296 / 280; 8 points of 7372800 451 / 478; double, 4 points, 455 / 423).
+inline int middle_groups(long long items, int grid2, bool fp64) {
+  const int most = fp64 || grid2 < 4096 ? grid2 : 4096;
+  return items < most ? (int)items : most;
+}
+
 }  // namespace fcas

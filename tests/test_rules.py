@@ -53,3 +53,11 @@ def test_direct_calls(rule, points, tiles, threads, fp64, n_det, direct):
 def test_fused_schedule(rule, items, fused):
     """The fused schedule takes points of few work items."""
     assert rule("fused", items) == fused
+
+
+@pytest.mark.parametrize("items,grid2,fp64,groups", [
+    (1024, 16384, 0, 1024), (4096, 16384, 0, 4096), (4097, 16384, 0, 4096), (4097, 2048, 0, 2048), (1 << 33, 4096, 0, 4096),
+    (4097, 16384, 1, 4097), (1 << 20, 16384, 1, 16384), (1 << 33, 1, 1, 1),
+])
+def test_middle_pass_groups(rule, items, grid2, fp64, groups):
+    assert rule("middle", items, grid2, fp64) == groups
