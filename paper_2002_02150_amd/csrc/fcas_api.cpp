@@ -530,6 +530,16 @@ EvalBufs own_bufs(const fcas_ctx* ctx) {
                   ctx->d_ws, ctx->ws_bytes, ctx->cfg.max_batch};
 }
 
+// In-band bins of the longest segment length in use.
+int64_t longest_bins(const fcas_ctx* ctx) {
+  int64_t n = 0;
+  for (int plan = 0; plan < kNumPlans; ++plan)
+    if (ctx->plan_refs[plan] > 0) n = std::max(n, kPlans[plan].n);
+  int k_lo = 0, k_hi = -1;
+  if (n > 0) band(ctx->cfg, n, &k_lo, &k_hi);
+  return k_hi - k_lo + 1;
+}
+
 // Enqueues the per-point set-up: descriptors and the per-plan work lists (their counts are zero between calls: the context starts
 // with zeros and every finalize clears them once the passes are done).
 int enqueue_setup(fcas_ctx* ctx, const EvalBufs& b, int32_t n, const double* d_theta, const int32_t* d_seg,
@@ -806,7 +816,7 @@ int fitness_grad_batch(fcas_ctx* ctx, int32_t n, const double* d_theta, const in
   hipStream_t s = (hipStream_t)hip_stream;
   if ((rc = enqueue_eval(ctx, n, d_theta, d_seg, d_fitness, d_argmax, s))) return rc;
   hipError_t e = launch_gradient(ctx->prec, ctx->grad, ctx->d_net, ctx->d_segs, ctx->d_evals, d_theta, d_argmax, n,
-                                 ctx->net.n_det, d_grad, s);
+                                 ctx->net.n_det, d_grad, longest_bins(ctx), s);
   if (e != hipSuccess) return hip_fail(e, "gradient launch");
   return FCAS_OK;
 }
@@ -825,11 +835,12 @@ int enqueue_polish(fcas_ctx* ctx, int32_t n, double* d_theta, const int32_t* d_s
   points.evals = ctx->d_pol_evals;
   if ((rc = enqueue_eval(ctx, points, n, d_theta, d_seg, d_fitness, d_argmax, s))) return rc;
   const int m = n * n_trials;
+  const int64_t bins = longest_bins(ctx);
   for (int step = 0; step < n_steps; ++step) {
-    if ((e = launch_adjoint(ctx->prec, ctx->grad, ctx->d_segs, points.evals, d_argmax, n, ctx->net.n_det, s)) !=
+    if ((e = launch_adjoint(ctx->prec, ctx->grad, ctx->d_segs, points.evals, d_argmax, n, ctx->net.n_det, bins, s)) !=
             hipSuccess ||
         (e = launch_polish_trials(ctx->grad, ctx->d_net, ctx->d_segs, points.evals, d_theta, d_seg, n, ctx->net.n_det,
-                                  n_trials, step_frac, ctx->d_pol_cand, b.evals, b.lists, b.counts, b.list_stride,
+                                  n_trials, step_frac, ctx->d_pol_cand, b.evals, b.lists, b.counts, b.list_stride, bins,
                                   ctx->d_err, s)) != hipSuccess)
       return hip_fail(e, "polish launch");
     if ((rc = enqueue_passes(ctx, b, m, nullptr, nullptr, s, true, true, false))) {

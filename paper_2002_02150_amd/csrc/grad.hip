@@ -396,12 +396,17 @@ __global__ void __launch_bounds__(64) k_polish_select(const NetDesc* __restrict_
   setup_group(net, q, th_s, e, k == 0, evals, nullptr, nullptr, 0, 0, err);
 }
 
+// Detectors per adjoint block: every detector up to four (24 registers of
+// sums each), networks of five to eight in two groups.
+static int adj_group(int n_det) { return n_det <= 4 ? n_det : (n_det + 1) / 2; }
+static int grad_parts(int n, int n_det, int64_t bins) { return adjoint_parts(n, n_det <= 4 ? 1 : 2, bins); }
+
 hipError_t launch_polish_trials(const GradBuffers& g, const NetDesc* net, const SegDesc* segs, const EvalDesc* evals,
                                 const double* theta, const int32_t* seg, int n, int n_det, int trials,
                                 double step_frac, double* cand, EvalDesc* trial_evals, int32_t* lists,
-                                int32_t* counts, int list_stride, int32_t* err, hipStream_t s) {
+                                int32_t* counts, int list_stride, int64_t bins, int32_t* err, hipStream_t s) {
   hipLaunchKernelGGL(k_polish_trials, dim3(n), dim3(64), 0, s, net, segs, evals, theta, seg, g.sums,
-                     grad_parts(n, n_det), trials, step_frac, cand, trial_evals, lists, counts, list_stride, err);
+                     grad_parts(n, n_det, bins), trials, step_frac, cand, trial_evals, lists, counts, list_stride, err);
   return hipGetLastError();
 }
 
@@ -422,22 +427,11 @@ hipError_t launch_polish_select(int precision, const NetDesc* net, const SegDesc
   return hipGetLastError();
 }
 
-// Detectors per adjoint block: every detector up to four (24 registers of
-// sums each), networks of five to eight in two groups.
-static int adj_group(int n_det) { return n_det <= 4 ? n_det : (n_det + 1) / 2; }
-
-int grad_parts(int n, int n_det) {
-  // enough blocks to cover the chip for small batches, one part for large ones
-  const int groups = n_det <= 4 ? 1 : 2;
-  int parts = (kAdjMinBlocks + n * groups - 1) / (n * groups);
-  return parts < 1 ? 1 : (parts > kAdjMaxParts ? kAdjMaxParts : parts);
-}
-
 int alloc_grad_buffers(GradBuffers& g, int max_batch, int n_det) {
   g.max_batch = max_batch;
   g.n_det = n_det;
-  // n * parts <= n + kAdjMinBlocks for every n
-  const size_t entries = ((size_t)max_batch + kAdjMinBlocks) * n_det;
+  // n * adjoint_parts(n, ...) <= n + 1024 for every n
+  const size_t entries = ((size_t)max_batch + 1024) * n_det;
   const size_t bytes = entries * kAdjSums * 2 * sizeof(double);
   if (hipMalloc((void**)&g.sums, bytes) != hipSuccess) {
     g.sums = nullptr;
@@ -452,8 +446,8 @@ void free_grad_buffers(GradBuffers& g) {
 }
 
 hipError_t launch_adjoint(int precision, const GradBuffers& g, const SegDesc* segs, const EvalDesc* evals,
-                          const int32_t* argmax, int n, int n_det, hipStream_t s) {
-  const int parts = grad_parts(n, n_det);
+                          const int32_t* argmax, int n, int n_det, int64_t bins, hipStream_t s) {
+  const int parts = grad_parts(n, n_det, bins);
   const int dt = adj_group(n_det);
   const dim3 grid(n, (n_det + dt - 1) / dt, parts), block(kAdjThreads);
 #define FCAS_ADJOINT(DT)                                                                                    \
@@ -479,10 +473,10 @@ hipError_t launch_adjoint(int precision, const GradBuffers& g, const SegDesc* se
 
 hipError_t launch_gradient(int precision, const GradBuffers& g, const NetDesc* net, const SegDesc* segs,
                            const EvalDesc* evals, const double* theta, const int32_t* argmax, int n, int n_det,
-                           double* grad, hipStream_t s) {
-  const hipError_t e = launch_adjoint(precision, g, segs, evals, argmax, n, n_det, s);
+                           double* grad, int64_t bins, hipStream_t s) {
+  const hipError_t e = launch_adjoint(precision, g, segs, evals, argmax, n, n_det, bins, s);
   if (e != hipSuccess) return e;
-  const int parts = grad_parts(n, n_det);
+  const int parts = grad_parts(n, n_det, bins);
   hipLaunchKernelGGL(k_chain, dim3(n), dim3(64), 0, s, net, segs, evals, theta, g.sums, parts, n, grad);
   return hipGetLastError();
 }

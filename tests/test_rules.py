@@ -61,3 +61,14 @@ def test_fused_schedule(rule, items, fused):
 ])
 def test_middle_pass_groups(rule, items, grid2, fp64, groups):
     assert rule("middle", items, grid2, fp64) == groups
+
+
+@pytest.mark.parametrize("points,groups,bins,parts", [
+    (1, 1, 62080, 64), (1, 2, 62080, 64), (16, 1, 62080, 64), (17, 1, 62080, 61), (1024, 1, 62080, 1), (1 << 24, 2, 62080, 1),
+    (1, 1, 1746000, 106), (1, 1, 3492000, 213), (1, 2, 1 << 28, 256), (4, 1, 1 << 28, 256), (5, 1, 1 << 28, 205),
+    (1, 1, 1, 64),
+])
+def test_adjoint_parts(rule, points, groups, bins, parts):
+    """And no more sums than a context holds: points + 1024 per detector."""
+    assert rule("adjoint", points, groups, bins) == parts
+    assert points * parts <= points + 1024
