@@ -124,8 +124,11 @@ int fcas_plan_info(int32_t plan, int64_t* n_samples, int32_t* n1, int32_t* n2, i
                    int32_t* cols, int32_t* rows);
 
 /* Use plan `plan` for segments of its length registered after this call, with
- * grid1 / grid2 persistent work-groups for its first and last passes (grid2
- * also sizes a three-pass plan's middle pass; 0 = default).
+ * grid1 / grid2 persistent work-groups for its first and last passes (0 =
+ * default): as many sets of one for each work item of a point as that number
+ * holds, at least one set and at most one per point.  grid2 also sizes a
+ * three-pass plan's middle pass (FCAS_MIXED: up to 4096), and small calls give
+ * every work item of pass 1 a work-group whatever grid1 says.
  * This is how the autotuner's choice is applied.  FCAS_EINVAL for a plan out
  * of range or grid sizes outside [0, 2^20]. */
 int fcas_select_plan(fcas_ctx* ctx, int32_t plan, int32_t grid1, int32_t grid2);
