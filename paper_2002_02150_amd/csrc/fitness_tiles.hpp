@@ -693,34 +693,40 @@ FCAS_HD void passm_fetch(cplx<Real> (&v)[S][PL::EM], const cplx<Real>* slot, int
   }
 }
 
-// w_N^{j1 (km N2 + k2)} on input: exact at q = 0, then advanced by
-// w_N^{j1 PM N2} from register to register.
+// The middle pass's twiddles are exact at registers 0 and kPassmExact, and
+// advanced by a constant factor from register to register between: half the
+// steps leave half the error of one run over all registers, which dominated that
+// of the long lengths.
+constexpr int kPassmExact = 8;
+
+// w_N^{j1 (km N2 + k2)} on input, advanced by w_N^{j1 PM N2}.
 template <typename Real, class PL, int S>
 FCAS_HD void passm_twiddle_in(cplx<Real> (&v)[S][PL::EM], int tile, int c, int p) {
   int j1, k2;
   passm_coords<PL>(tile, c, j1, k2);
-  cplx<Real> t = twiddle<Real>(j1 * (p * PL::N2 + k2), (int)PL::N);     // < N1 W1 = N
   const cplx<Real> st = twiddle<Real>(j1 * (PL::PM * PL::N2), (int)PL::N);
+  cplx<Real> t = st;
 #pragma unroll
   for (int q = 0; q < PL::EM; ++q) {
+    t = q % kPassmExact == 0 ? twiddle<Real>(j1 * ((p + q * PL::PM) * PL::N2 + k2), (int)PL::N)   // < N1 W1 = N
+                             : mul(t, st);
 #pragma unroll
     for (int s = 0; s < S; ++s) v[s][q] = mul(v[s][q], t);
-    if (q + 1 < PL::EM) t = mul(t, st);
   }
 }
 
-// w_{NM N2}^{jm k2} on output: exact at q = 0, then advanced by w_{NM N2}^{PM k2}.
+// w_{NM N2}^{jm k2} on output, advanced by w_{NM N2}^{PM k2}.
 template <typename Real, class PL, int S>
 FCAS_HD void passm_twiddle_out(cplx<Real> (&v)[S][PL::EM], int tile, int c, int p) {
   int j1, k2;
   passm_coords<PL>(tile, c, j1, k2);
-  cplx<Real> t = twiddle<Real>(p * k2, PL::W1);                      // < PM N2 <= W1
   const cplx<Real> st = twiddle<Real>(PL::PM * k2, PL::W1);
+  cplx<Real> t = st;
 #pragma unroll
   for (int q = 0; q < PL::EM; ++q) {
+    t = q % kPassmExact == 0 ? twiddle<Real>((p + q * PL::PM) * k2, PL::W1) : mul(t, st);   // < NM N2 = W1
 #pragma unroll
     for (int s = 0; s < S; ++s) v[s][q] = mul(v[s][q], t);
-    if (q + 1 < PL::EM) t = mul(t, st);
   }
 }
 
