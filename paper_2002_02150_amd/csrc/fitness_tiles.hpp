@@ -693,41 +693,46 @@ FCAS_HD void passm_fetch(cplx<Real> (&v)[S][PL::EM], const cplx<Real>* slot, int
   }
 }
 
-// The middle pass's twiddles are exact at registers 0 and kPassmExact, and
-// advanced by a constant factor from register to register between: half the
-// steps leave half the error of one run over all registers, which dominated that
-// of the long lengths.
-constexpr int kPassmExact = 8;
+// Multiplies register q of every series by t st^(q - EM/2): exact in the middle,
+// advanced by a constant factor from register to register upwards and downwards
+// from there.  (Half the steps of one run over all registers leave half its
+// error, which dominated that of the long lengths.)
+template <typename Real, int EM, int S>
+FCAS_HD void passm_twiddle(cplx<Real> (&v)[S][EM], cplx<Real> t, cplx<Real> st) {
+  constexpr int MID = EM / 2;
+  const cplx<Real> back = mk<Real>(st.x, -st.y);
+  cplx<Real> up = t, down = mul(t, back);
+#pragma unroll
+  for (int q = MID; q < EM; ++q) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) v[s][q] = mul(v[s][q], up);
+    if (q + 1 < EM) up = mul(up, st);
+  }
+#pragma unroll
+  for (int q = MID - 1; q >= 0; --q) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) v[s][q] = mul(v[s][q], down);
+    if (q > 0) down = mul(down, back);
+  }
+}
 
-// w_N^{j1 (km N2 + k2)} on input, advanced by w_N^{j1 PM N2}.
+// w_N^{j1 (km N2 + k2)} on input.
 template <typename Real, class PL, int S>
 FCAS_HD void passm_twiddle_in(cplx<Real> (&v)[S][PL::EM], int tile, int c, int p) {
   int j1, k2;
   passm_coords<PL>(tile, c, j1, k2);
-  const cplx<Real> st = twiddle<Real>(j1 * (PL::PM * PL::N2), (int)PL::N);
-  cplx<Real> t = st;
-#pragma unroll
-  for (int q = 0; q < PL::EM; ++q) {
-    t = q % kPassmExact == 0 ? twiddle<Real>(j1 * ((p + q * PL::PM) * PL::N2 + k2), (int)PL::N)   // < N1 W1 = N
-                             : mul(t, st);
-#pragma unroll
-    for (int s = 0; s < S; ++s) v[s][q] = mul(v[s][q], t);
-  }
+  passm_twiddle<Real, PL::EM, S>(
+      v, twiddle<Real>(j1 * ((p + PL::EM / 2 * PL::PM) * PL::N2 + k2), (int)PL::N),   // < N1 W1 = N
+      twiddle<Real>(j1 * (PL::PM * PL::N2), (int)PL::N));
 }
 
-// w_{NM N2}^{jm k2} on output, advanced by w_{NM N2}^{PM k2}.
+// w_{NM N2}^{jm k2} on output.
 template <typename Real, class PL, int S>
 FCAS_HD void passm_twiddle_out(cplx<Real> (&v)[S][PL::EM], int tile, int c, int p) {
   int j1, k2;
   passm_coords<PL>(tile, c, j1, k2);
-  const cplx<Real> st = twiddle<Real>(PL::PM * k2, PL::W1);
-  cplx<Real> t = st;
-#pragma unroll
-  for (int q = 0; q < PL::EM; ++q) {
-    t = q % kPassmExact == 0 ? twiddle<Real>((p + q * PL::PM) * k2, PL::W1) : mul(t, st);   // < NM N2 = W1
-#pragma unroll
-    for (int s = 0; s < S; ++s) v[s][q] = mul(v[s][q], t);
-  }
+  passm_twiddle<Real, PL::EM, S>(v, twiddle<Real>((p + PL::EM / 2 * PL::PM) * k2, PL::W1),   // < NM N2 = W1
+                                 twiddle<Real>(PL::PM * k2, PL::W1));
 }
 
 // Store B2[m][j1][jm N2 + k2], over the elements the tile loaded.
